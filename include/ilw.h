@@ -158,7 +158,7 @@ int ilw_residual_add(const int8_t* a, const int8_t* b, int8_t* y, int64_t n,
  * windows tile the grid (LW-DETR's window attention).  head_dim 32 or 64
  * (the decoder's 8 heads of 32 channels, the encoder's heads of 64);
  * dim == heads * head_dim; tokens per window in [1, 2048].  The workspace
- * (ilw_attention_workspace_bytes) holds the window-major Q, K and V^T copies,
+ * (ilw_attention_workspace_bytes) holds the window-major Q, K and V copies,
  * rows of 64 bytes per head.
  */
 typedef struct {

@@ -205,7 +205,7 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // an offset from a null pointer is undefined.
 int8_t* carve(int8_t* base, size_t off) { return base ? base + off : nullptr; }
 
-// Window-major Q/K/V^T buffers carved from a workspace.
+// Window-major Q/K/V buffers carved from a workspace.
 size_t qkv_bytes(int32_t batch, const Geometry& g, int32_t D, QkvLayout* L, int8_t* base,
                  int32_t hd = 64) {
   const int32_t H = D / hd;
@@ -368,9 +368,9 @@ hipError_t pack_block_weights(const ilw_block_params* const* ps, const BlockLayo
   return flush();
 }
 
-// Workspace of one block: h | Q K V^T | att | x1 | g.  qkv_reserve (when
-// larger than this block's need) fixes the size of the Q K V^T region, so
-// that in an encoder every block's att buffer lies past every block's Q K V^T.
+// Workspace of one block: h | Q K V | att | x1 | g.  qkv_reserve (when
+// larger than this block's need) fixes the size of the Q K V region, so
+// that in an encoder every block's att buffer lies past every block's Q K V.
 size_t block_layout(const ilw_block_params* p, int32_t batch, const Geometry& g,
                     int8_t* base, BlockLayout* out, size_t qkv_reserve = 0,
                     bool with_packed = true) {
@@ -476,9 +476,9 @@ bool use_tail(const ilw_block_params* p, const ilw_block_params* next, int64_t M
 // What the previous block already left for this one in the workspace.
 enum { READY_NONE = 0, READY_H = 1, READY_QKV = 2 };
 
-// One encoder block: h = LN1(x) and Q, K, V^T (unless already there),
+// One encoder block: h = LN1(x) and Q, K, V (unless already there),
 // attention, then either the block tail kernel (which also leaves the next
-// block's Q, K, V^T in next_qkv) or projection + residual (+ LN2), fc1 +
+// block's Q, K, V in next_qkv) or projection + residual (+ LN2), fc1 +
 // GELU and fc2 + residual (+ the next block's LN1 in h).
 int run_block(const ilw_block_params* p, const ilw_block_params* next,
               const QkvLayout* next_qkv, const int8_t* x, int8_t* y, int32_t batch,
@@ -490,7 +490,7 @@ int run_block(const ilw_block_params* p, const ilw_block_params* next,
   hipError_t he = hipSuccess;
   *ready_out = READY_NONE;
 
-  // h = LN1(x) and Q, K, V^T in one launch where the tail kernel runs
+  // h = LN1(x) and Q, K, V in one launch where the tail kernel runs
   if (ready == READY_NONE && use_tail(p, nullptr, M)) {
     TailArgs ha = {};
     ha.x = x;
@@ -673,7 +673,7 @@ int check_encoder(const ilw_block_params* blocks, int32_t n_blocks, const int32_
   return ILW_OK;
 }
 
-// Largest Q K V^T region over the blocks of an encoder.
+// Largest Q K V region over the blocks of an encoder.
 size_t encoder_qkv_reserve(const ilw_block_params* blocks, int32_t n_blocks,
                            const int32_t* windows, int32_t batch, int32_t grid_h,
                            int32_t grid_w) {
@@ -1095,9 +1095,9 @@ int ilw_encoder_forward(const ilw_block_params* blocks, int32_t n_blocks,
   REQUIRE(aligned16(workspace), ILW_E_PARAM, "workspace must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
   // Block b reads its input from x (b = 0) or y and writes y.  The workspace
-  // regions h and Q K V^T sit at the same offsets for every block, so block
+  // regions h and Q K V sit at the same offsets for every block, so block
   // b can leave block b + 1's LN1 output (fused fc2 epilogue) or its Q, K,
-  // V^T (block tail kernel) there.
+  // V (block tail kernel) there.
   const size_t qres = encoder_qkv_reserve(blocks, n_blocks, windows, batch, grid_h, grid_w);
   // the 384-channel LayerNorm-fused linears read their weights packed in
   // MFMA fragment order: every block's are packed first, in one launch

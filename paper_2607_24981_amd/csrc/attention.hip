@@ -1,28 +1,33 @@
 // attention.hip -- fused integer attention for one (image, window, head,
 // block of query rows) per workgroup:
 //
-//   S = Q K^T (MFMA int8) -> per-tensor dyadic -> int8 scores held in LDS
-//   P = Constrained Shiftmax of every score row (Alg. 2)      (int8 in LDS)
+//   S = Q K^T (MFMA int8) -> per-tensor dyadic -> int8 scores
+//   P = Constrained Shiftmax of every score row (Alg. 2)
 //   O = P V   (MFMA int8) -> per-tensor dyadic -> int8 output (token order)
 //
 // Constrained Shiftmax needs the exact row maximum before any exponential
 // (ShiftExp of x - max cannot be rescaled bit-exactly when the maximum
-// changes), so a whole block of score rows is kept in LDS instead of the
-// online rescaling used by float attention: R rows x Tw int8 scores (51 KB
-// for 32 rows at Tw = 1600).  Because the scores are int8, max - score only
-// takes the values 0..254: ShiftExp is one 256-entry table per workgroup,
-// looked up once per score; the looked-up values stay in registers for the
-// normalization, and S_sum >> s_d is exactly the quotient-remainder
-// denominator of Alg. 2.
+// changes), so every score of a row is held until the maximum is known.  The
+// scores, then their exponentials, stay in registers from the first matmul to
+// the second: the waves of a workgroup split the keys of its R query rows in
+// blocks of 16, and a lane holds 4 consecutive keys of one row per block.
+// Those are also 4 bytes of the P V product's B operand once the key order of
+// the contraction is permuted, which V's layout does (blocks of 16 keys, see
+// QkvLayout), so neither scores nor probabilities pass through LDS.  Only the
+// row maxima, the row sums and the waves' partial P V sums cross waves.
 //
-// Per score, the exact integer work is a handful of VALU operations while the
-// two matmuls are 256 int8 MFMA ops (about two VALU lane-ops at the chip's
-// MFMA:VALU ratio), so this kernel is bound by the VALU work of the exact
-// Shiftmax, not by the matrix cores.
-#include <map>
-#include <mutex>
-#include <utility>
-
+// Because the scores are int8, max - score takes the values 0..254 and
+// ShiftExp is one 256-entry table; S_sum >> s_d is exactly the
+// quotient-remainder denominator of Alg. 2.
+//
+// Bound: VALU instructions.  gfx950 issues the 64-bit multiply-add, the
+// permutes and the medians at one rate, 4 cycles per wave, so their number is
+// what counts: about 10.5 per 64 scores (7 of them requantize, address the
+// table, sum, multiply and pack) against 12 with score rows in LDS; the two
+// matmuls take a tenth of the time beside them.  Measured against 32-row
+// blocks whose scores and probabilities went through LDS, on 1600-key rows
+// (2400 workgroups) 64.4 -> 59.0 us, 1200 workgroups 36.7 -> 30.5 us, 400-key
+// windows (4992 workgroups) 40.8 -> 34.8 us.
 #include "ilw_internal.h"
 
 namespace ilw {
@@ -30,579 +35,594 @@ namespace {
 
 constexpr int kXcds = 8;  // accelerator complex dies, each with its own L2
 
-// Score requantization, stored biased: the result is q + 128 in [1, 255]
-// (q in [-127, 127]).  c = 2^(s-1) + 128 * 2^s, so
-//   floor((acc * m + c) / 2^s) = floor((acc * m + 2^(s-1)) / 2^s) + 128,
-// exact in 64 bits (|acc| <= 64 * 128 * 128 = 2^20 for a 64-channel head,
-// |m| < 2^31 and s <= 54).  The host checks that this value always fits in
-// int32 (always true for s >= 32); then the low word of the 64-bit shift is
-// the value itself and one clamp finishes the job.
-__device__ __forceinline__ int32_t rq_fast(int32_t acc, int32_t mult, int64_t c, int32_t shift) {
-  const int64_t v = ((int64_t)acc * mult + c) >> shift;
-  return min(max((int32_t)v, 128 + kQmin), 128 + kQmax);
+// Copies of the ShiftExp table: lane l reads copy l % kCopies, entry d at word
+// kCopies d + l % kCopies, so that few lanes of a lookup meet on an LDS bank
+// (with one copy a lookup of spread scores takes 5.5 LDS cycles; 32 copies
+// against 16 are 1% faster on the medium encoder, and free: the P V sums need
+// the bytes later).
+constexpr int kCopies = 32;
+constexpr int kRow = kCopies * 4;  // bytes per table entry
+
+// Slots of 16 keys whose exponentials a wave keeps in registers, of nb; the
+// scores of the others are kept as bytes and looked up twice (for the sum, and
+// again for P), which keeps the kernel within the 128 registers of four waves
+// per SIMD (16 more slots' worth would be spilled).
+constexpr int full_slots(int nb) { return nb <= 10 ? nb : nb <= 12 ? 10 : nb <= 14 ? 9 : 8; }
+
+// The scores are kept complemented, n = ~q = -q - 1 in [-128, 126]: the row
+// maximum of q is the row minimum of n, and max - q = n - min.
+//   ~floor((acc m + r) / 2^s) = floor((-acc m - r - 1) / 2^s),
+// so with nm = -m and c = -2^(s-1) - 1 the complement costs nothing.  For s in
+// [32, 54] the shift is one of the product's high word: |acc| <= 2^20 for a
+// 64-channel head and |m| < 2^31, so the 64-bit sum is exact and the shifted
+// high word is the value itself.
+__device__ __forceinline__ int32_t score_fast(int32_t acc, int32_t nm, int64_t c, int32_t s32) {
+  const int32_t v = (int32_t)(((int64_t)acc * nm + c) >> 32) >> s32;
+  return min(max(v, ~kQmax), ~kQmin);
 }
 
-// Otherwise (any s up to 62) the accumulator is clamped to [-L, L] first:
+// Otherwise (any s in [1, 62]) the accumulator is clamped to [-L, L] first:
 // that keeps every saturated result saturated and the shifted value inside
-// int32; rnd = 2^(s-1) and the bias is added after the shift.
-__device__ __forceinline__ int32_t rq_clamped(int32_t acc, int32_t L, int32_t mult,
-                                              int64_t rnd, int32_t shift) {
+// int32.
+__device__ __forceinline__ int32_t score_clamped(int32_t acc, int32_t L, int32_t mult,
+                                                 int64_t rnd, int32_t shift) {
   acc = min(max(acc, -L), L);
   const int64_t v = ((int64_t)acc * mult + rnd) >> shift;
-  return min(max((int32_t)v, kQmin), kQmax) + 128;
+  return ~min(max((int32_t)v, kQmin), kQmax);
 }
 
-// Bytes 0 of a, b, c, d packed into one word (a in the low byte).
-__device__ __forceinline__ uint32_t pack_bytes(int32_t a, int32_t b, int32_t c, int32_t d) {
-  const uint32_t lo = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
-  const uint32_t hi = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);
+// Ends a step of an unrolled loop: neither loads nor arithmetic move across,
+// which keeps a step's temporaries from being live in its neighbours.  The
+// running values listed are computed by then.
+__device__ __forceinline__ void step_end() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <typename T, typename... More>
+__device__ __forceinline__ void step_end(T& v, More&... more) {
+  asm volatile("" : "+v"(v));
+  step_end(more...);
+}
+
+// Bytes 0 of a, b, c, d packed into one word.
+__device__ __forceinline__ uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u);
+  const uint32_t hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
   return lo | (hi << 16);
 }
 
-// NW waves per workgroup (4, 8 or 16): keys are split over all waves for the
-// scores, rows for the Shiftmax (R / NW rows per wave), and (channel group,
-// key range) pairs for P V, whose int32 partial sums are added through LDS.
-// MASK says which Shiftmax words may hold no key: 0 any word past the keys
-// (whole words, T_w % 4 == 0), 1 any byte past the keys (T_w % 4 != 0),
-// 2 only the last word step's (T_w = Twp and (JW - 1) LPR <= Twp / 4),
-// 3 only the last two steps' (whole words, JW LPR = Twp / 4 and
-// (JW - 2) LPR <= T_w / 4: every step stays inside the row).
-template <int R, int LPR, bool NARROW, int MASK, int NW, int JW, bool P3K>
-__global__ __launch_bounds__(64 * NW) void attention_kernel(AttnArgs a, int32_t lds_row,
-                                                            int32_t clampL, int32_t nrb,
-                                                            int64_t ntiles) {
-  constexpr bool RAGGED = MASK == 1;
-  extern __shared__ __attribute__((aligned(16))) int8_t sS[];  // [R][lds_row]
-  __shared__ uint32_t elut[256];
-  __shared__ int32_t pmax[NW][R];
-  constexpr int KP = NW / 4;  // key ranges of the P V phase
-  __shared__ v4i ored[KP > 1 ? (KP - 1) * 4 * (R / 16) * 64 : 1];
+template <bool FAST>
+struct SumType {
+  typedef uint64_t type;
+};
+template <>
+struct SumType<true> {
+  typedef uint32_t type;
+};
 
-  constexpr int NF = R / 16;  // query fragments of 16 rows
+// R query rows (16 or 32) per workgroup of NW waves; wave w takes the 16-key
+// blocks w, w + NW, ... : NB slots, of which only the last can be missing or
+// partial (NB = ceil(blocks / NW)).  FAST: the host has shown (launch_attention)
+// that the scores take the high-word form, that a wave's sum of a row's 16 NB
+// exponentials stays below 2^32, and that P is one multiply without a clamp.
+template <int R, int NW, int NB, bool FAST>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
+void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
+  constexpr int NF = R / 16;                      // query fragments of 16 rows
+  constexpr int NBF = full_slots(NB);             // slots held as exponentials
+  constexpr int NPK = NB - NBF;                   // slots held as bytes
+  // The table's copies; once the exponentials are looked up the same bytes
+  // hold the partial P V sums [wave][channel group][fragment][lane].
+  constexpr int PARTS = NW * 4 * NF * 64;  // 16-byte words
+  constexpr int TAB = 256 * kRow;
+  __shared__ __attribute__((aligned(1024))) int8_t sbuf[PARTS * 16 > TAB ? PARTS * 16 : TAB];
+  __shared__ __attribute__((aligned(16))) int32_t pmin[R][NW];
+  typedef typename SumType<FAST>::type Sum;
+  __shared__ __attribute__((aligned(16))) Sum psum[R][NW];
+
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform
-  const int32_t Tw = a.Tw, Twp = a.Twp;
+  const int32_t Tw = a.Tw;
   // Workgroups go to the 8 XCDs round-robin; XCD x takes the contiguous
   // tiles x * per + min(x, rem) + ..., so the row blocks of one (window,
   // head) share one XCD's L2 for their keys and values.
-  const int64_t bid = blockIdx.x;
-  const int64_t per = ntiles / kXcds, rem = ntiles % kXcds, xcd = bid % kXcds;
-  const int64_t tile = xcd * per + (xcd < rem ? xcd : rem) + bid / kXcds;
-  const int64_t hs = tile / nrb;  // bw * H + h
-  const int32_t i0 = (int32_t)(tile - hs * nrb) * R;
-  const int32_t h = (int32_t)(hs % a.H);
-  const int32_t bw = (int32_t)(hs / a.H);  // image * nW + window
-  const int64_t slice = (int64_t)bw * a.H + h;
-  const int8_t* __restrict__ Q = a.q + slice * Tw * 64;
-  const int8_t* __restrict__ K = a.k + slice * Tw * 64;
-  const int8_t* __restrict__ Vt = a.vt + slice * 64 * Twp;
+  const uint32_t bid = blockIdx.x;
+  const uint32_t per = ntiles / kXcds, rem = ntiles % kXcds, xcd = bid % kXcds;
+  const uint32_t tile = xcd * per + min(xcd, rem) + bid / kXcds;
+  const uint32_t slice = tile / nrb;  // (image * nW + window) * H + head
+  const int32_t i0 = (int32_t)(tile - slice * nrb) * R;
+  const int8_t* __restrict__ Q = a.q + (int64_t)slice * Tw * 64;
+  const int8_t* __restrict__ K = a.k + (int64_t)slice * Tw * 64;
+  const int8_t* __restrict__ V = a.vt + (int64_t)slice * 64 * a.Twp;
 
-  // ShiftExp(-d) for d = 0..254 (entry 255 is never a valid max - score)
-  if (tid < 256) elut[tid] = tid < 255 ? (uint32_t)shift_exp(-tid, a.I0, a.k_inter) : 0u;
+  const int32_t nkb = (Tw + 15) >> 4;
+  // slot j: block wave + j NW; the last slot may be missing in this wave
+  // (uniform bases and one 32-bit lane offset each, so the addresses take no
+  // vector arithmetic)
+  const uint32_t krow = (lane & 15) * 64 + (lane >> 4) * 16;
+  auto kload = [&](int j) {
+    if (j < NB - 1) return *(const v4i*)(K + (wave + j * NW) * 1024 + krow);
+    // keys past the window repeat the last one: they never change the maximum
+    const uint32_t key = min((wave + j * NW) * 16 + (lane & 15), Tw - 1);
+    return *(const v4i*)(K + (key * 64 + (lane >> 4) * 16));
+  };
 
   // Query fragments (MFMA B operand: columns = query rows).  Rows past the
   // window are clamped to a valid row; their results are never stored.
   // Past the head dimension (32-dim heads) the query fragment is zero, so
   // the unused key bytes there contribute nothing.
-  const v4i zero4 = {0, 0, 0, 0};
+  const v4i zero = {0, 0, 0, 0};
   v4i qf[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    const int32_t r = min(i0 + f * 16 + (lane & 15), Tw - 1);
-    qf[f] = *(const v4i*)(Q + (int64_t)r * 64 + (lane >> 4) * 16);
-    if ((lane >> 4) * 16 >= a.hd) qf[f] = zero4;
+    const uint32_t r = min(i0 + f * 16 + (lane & 15), Tw - 1);
+    qf[f] = *(const v4i*)(Q + (r * 64 + (lane >> 4) * 16));
+  }
+  constexpr int RING = NB < 4 ? NB : 4;  // key fragments in flight
+  v4i kr[RING];
+#pragma unroll
+  for (int j = 0; j < RING; ++j) kr[j] = kload(j);
+  if ((lane >> 4) * 16 >= a.hd) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) qf[f] = zero;
   }
 
-  // ---- phase 1: scores.  Waves split the keys in blocks of 16; the key
-  // fragment is the A operand, so a lane holds 4 consecutive keys of one row.
-  // Scores and row maxima are kept biased (q + 128).
-  const v4i zero = {0, 0, 0, 0};
-  const int32_t sm = a.score_mult, ss = a.score_shift;
-  const int64_t srnd = (int64_t)1 << (ss - 1);
-  const int64_t sc = srnd + (a.rq_fast ? (int64_t)128 << ss : 0);  // s <= 54 when fast
-  int32_t mx[NF];
+  // ShiftExp(-d) for d = 0..254 (entry 255, never a valid max - score, is 0),
+  // kCopies times; a thread starts its entry's 16-byte stores at another chunk
+  // than its neighbours
 #pragma unroll
-  for (int f = 0; f < NF; ++f) mx[f] = 0;
-  const int32_t nkb = (Tw + 15) >> 4;
-  const int32_t kc = (lane >> 4) * 4;  // first of this lane's 4 keys in a block
-  // The nkf whole 16-key blocks go through a ring of loads from a per-lane
-  // base (block kb, wave-uniform, clamped to the last whole block); a
-  // partial last block (T_w % 16 != 0) is done on its own afterwards, its
-  // keys past the window clamped to the last key.
-  const int32_t nkf = Tw >> 4;
-  const int8_t* const kbase = K + (lane & 15) * 64 + (lane >> 4) * 16;
-  auto kload = [&](int32_t kb) { return *(const v4i*)(kbase + (int64_t)min(kb, nkf - 1) * 1024); };
+  for (int d = tid; d < 256; d += 64 * NW) {
+    const uint32_t z = min((uint32_t)(d + ((d + 1) >> 1) - ((d + 15) >> 4)),
+                           (uint32_t)(a.k_inter * a.I0));
+    const uint32_t n = __umulhi(z, a.inv_I0);  // floor(z / I0), or z for I0 = 1
+    const uint32_t q = a.I0 == 1 ? z : n;
+    const uint32_t fr = z - q * (uint32_t)a.I0;
+    const int32_t e = d < 255 ? (a.I0 - (int32_t)((fr + 1) >> 1)) << (a.k_inter - (int32_t)q) : 0;
+    const v4i e4 = {e, e, e, e};
+#pragma unroll
+    for (int c = 0; c < kCopies / 4; ++c)
+      *(v4i*)(sbuf + d * kRow + ((c + d) % (kCopies / 4)) * 16) = e4;
+  }
+
+  // ---- phase 1: scores.  The key fragment is the A operand, so a lane holds
+  // 4 consecutive keys of row lane % 16 of each fragment.  The products of
+  // the next slot are issued before the current one is requantized.
+  int32_t sc[NBF][NF][4];  // complemented scores, then exponentials
+  uint32_t pk[NPK > 0 ? NPK : 1][NF];  // packed slots: complemented scores + 128, as bytes
+  int32_t mn[NF];
+#pragma unroll
+  for (int f = 0; f < NF; ++f) mn[f] = ~kQmin;
   auto phase1 = [&](auto fast) {
-    // requantize block kb's products, fold them into the row maxima and store
-    // them biased as bytes
-    auto emit = [&](int32_t kb, const v4i(&sc4)[NF]) {
-      const int32_t col = kb * 16 + kc;
+    const int32_t nm = -a.score_mult, s32 = a.score_shift - 32;
+    const int64_t rnd = (int64_t)1 << (a.score_shift - 1), c = -rnd - 1;
+    v4i pr[2][NF];  // products, alternating
+    auto products = [&](int j) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+        pr[j & 1][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kr[j % RING], qf[f], zero, 0, 0, 0);
+      if (j + RING < NB) kr[j % RING] = kload(j + RING);
+    };
+    auto emit = [&](int j) {
 #pragma unroll
       for (int f = 0; f < NF; ++f) {
-        int32_t v[4];
+        int32_t n[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          v[r] = decltype(fast)::value ? rq_fast(sc4[f][r], sm, sc, ss)
-                                       : rq_clamped(sc4[f][r], clampL, sm, srnd, ss);
-        // keys past the window repeat the last key (clamped rows), so they
-        // never raise the maximum
-        mx[f] = max(max(mx[f], v[0]), v[1]);
-        mx[f] = max(max(mx[f], v[2]), v[3]);
-        *(uint32_t*)(sS + (f * 16 + (lane & 15)) * lds_row + col) =
-            pack_bytes(v[0], v[1], v[2], v[3]);
+          n[r] = decltype(fast)::value
+                     ? score_fast(pr[j & 1][f][r], nm, c, s32)
+                     : score_clamped(pr[j & 1][f][r], a.score_clamp, a.score_mult, rnd,
+                                     a.score_shift);
+        mn[f] = min(min(mn[f], n[0]), n[1]);
+        mn[f] = min(min(mn[f], n[2]), n[3]);
+        if (j < NBF) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) sc[j < NBF ? j : 0][f][r] = n[r];
+        } else {
+          pk[j < NBF ? 0 : j - NBF][f] =
+              pack_bytes((uint32_t)n[0], (uint32_t)n[1], (uint32_t)n[2], (uint32_t)n[3]) ^
+              0x80808080u;
+        }
       }
     };
-    auto products = [&](v4i(&sc4)[NF], const v4i& kf) {
+    products(0);
 #pragma unroll
-      for (int f = 0; f < NF; ++f) sc4[f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf, qf[f], zero, 0, 0, 0);
-    };
-    if (nkf < nkb && wave == nkf % NW) {  // the partial last block
-      const int32_t key = min(nkf * 16 + (lane & 15), Tw - 1);
-      v4i sp[NF];
-      products(sp, *(const v4i*)(K + (int64_t)key * 64 + (lane >> 4) * 16));
-      emit(nkf, sp);
-    }
-    if (wave >= nkf) return;
-    // A ring of four key fragments in flight: slot u holds block kb + u NW
-    // and is reloaded with block kb + 4 NW once its products are issued.
-    // Loads past the last block re-read the clamped last key and are never
-    // used.  The products of the next block are issued before the current
-    // block is requantized, so the matrix core and the vector unit overlap;
-    // two product sets alternate.
-    v4i kr[4] = {kload(wave), kload(wave + NW), kload(wave + 2 * NW), kload(wave + 3 * NW)};
-    v4i s0[NF], s1[NF];
-    products(s0, kr[0]);
-    kr[0] = kload(wave + 4 * NW);
-    int32_t kb = wave;
-    // one block: kr slot U + 1 feeds the next block's products; true when kb
-    // was the last block
-    auto step = [&](auto U, v4i(&cur)[NF], v4i(&nxt)[NF]) {
-      constexpr int un = (decltype(U)::value + 1) & 3;
-      const bool more = kb + NW < nkf;
-      if (more) products(nxt, kr[un]);
-      emit(kb, cur);
-      if (!more) return true;
-      kr[un] = kload(kb + 5 * NW);
-      kb += NW;
-      return false;
-    };
-    for (;;) {
-      if (step(IntC<0>{}, s0, s1)) break;
-      if (step(IntC<1>{}, s1, s0)) break;
-      if (step(IntC<2>{}, s0, s1)) break;
-      if (step(IntC<3>{}, s1, s0)) break;
+    for (int j = 0; j < NB; ++j) {
+      if (j + 1 < NB) products(j + 1);
+      emit(j);
+      step_end(mn[0], mn[NF - 1]);
     }
   };
-  if (a.rq_fast)
+  if constexpr (FAST) {
     phase1(Flag<true>{});
-  else
-    phase1(Flag<false>{});
-  // row maxima: combine the 4 lanes sharing a row, then the waves
+  } else {
+    if (a.rq_fast)
+      phase1(Flag<true>{});
+    else
+      phase1(Flag<false>{});
+  }
+  // row minima: combine the 4 lanes sharing a row, then the waves
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    mx[f] = max(mx[f], __shfl_xor(mx[f], 16, 64));
-    mx[f] = max(mx[f], __shfl_xor(mx[f], 32, 64));
-    if (lane < 16) pmax[wave][f * 16 + lane] = mx[f];
+    mn[f] = min(mn[f], __shfl_xor(mn[f], 16, 64));
+    mn[f] = min(mn[f], __shfl_xor(mn[f], 32, 64));
+    if (lane < 16) pmin[f * 16 + lane][wave] = mn[f];
   }
-  __syncthreads();
+  lds_sync();  // also publishes the table
 
-  // ---- phase 2: Constrained Shiftmax of each row, in place.  LPR lanes
-  // share one row; a lane keeps the ShiftExp values of its elements in
-  // registers between the sum and the normalization.
+  // ---- phase 2: exponentials and their sums
+  int32_t base[NF];  // table address of score 0's exponential in this lane's copy
+  // the exponential of key r of the last slot: keys past the window have none
+  auto masked = [&](int r, int32_t e) {
+    return (wave + (NB - 1) * NW) * 16 + (lane >> 4) * 4 + r < Tw ? e : 0;
+  };
+  auto packed_exp = [&](int j, int f, int32_t(&e)[4]) {
+    // (opaque, so that the second lookup unpacks again instead of keeping the
+    // first one's four addresses)
+    asm volatile("" : "+v"(pk[j - NBF][f]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      e[r] = *(const int32_t*)(sbuf + (base[f] - 128 * kRow +
+                                       (int32_t)((pk[j - NBF][f] >> (8 * r)) & 255) * kRow));
+      if (j == NB - 1) e[r] = masked(r, e[r]);
+    }
+  };
   {
-    constexpr int RG = 64 / LPR;   // rows processed together by one wave
-    // JW words per lane: Twp / 4 <= JW * LPR (the host picks the smallest
-    // JW it has for the window)
-    const int sub = lane / LPR, k = lane % LPR;
-    const int32_t nword = Twp >> 2;
-    const int32_t pcap = (1 << (a.k_out - 1)) - 1;
-    const u16x2 pcap2 = {(unsigned short)pcap, (unsigned short)pcap};
-    static_assert(R / NW >= RG, "a wave must own at least RG rows");
-    for (int rr0 = wave * (R / NW); rr0 < (wave + 1) * (R / NW); rr0 += RG) {
-      const int rr = rr0 + sub;
-      uint32_t* row = (uint32_t*)(sS + rr * lds_row);
-      int32_t m = pmax[0][rr];
+    Sum sum[NF];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) m = max(m, pmax[w][rr]);
-      const uint32_t m4 = (uint32_t)m * 0x01010101u;  // biased maximum per byte
-      uint32_t e[JW][4];
-      uint64_t sum = 0;
-      uint32_t sum32 = 0;
+    for (int f = 0; f < NF; ++f) {
+      int32_t m = pmin[f * 16 + (lane & 15)][0];
 #pragma unroll
-      for (int j = 0; j < JW; ++j) {
-        const int32_t wd = k + j * LPR;
-        // a step that may pass the keys
-        const bool tail = MASK == 2 ? j == JW - 1 : (MASK == 3 ? j >= JW - 2 : true);
-        const uint32_t word = row[tail && MASK != 3 ? min(wd, nword - 1) : wd];  // inside the row
-        // max - score per byte (both biased): every valid byte is >= 0, and a
-        // borrow from an invalid (higher) byte never reaches a valid one.
-        // Words past the window index table entry 255, which is 0.
-        uint32_t d4 = m4 - word;
-        if (!RAGGED && tail) d4 = wd * 4 < Tw ? d4 : 0xffffffffu;
+      for (int w = 1; w < NW; ++w) m = min(m, pmin[f * 16 + (lane & 15)][w]);
+      base[f] = (lane & (kCopies - 1)) * 4 - m * kRow;
+      sum[f] = 0;
+    }
+    auto lookup = [&](int j, int f) {
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uint32_t ev = elut[(d4 >> (8 * b)) & 255];
-          if (RAGGED) ev = wd * 4 + b < Tw ? ev : 0u;
-          e[j][b] = ev;
-          if (NARROW) sum32 += ev; else sum += ev;
+      for (int r = 0; r < 4; ++r)
+        sc[j][f][r] = *(const int32_t*)(sbuf + (base[f] + sc[j][f][r] * kRow));
+    };
+    auto add = [&](const int32_t(&e)[4], int f) {  // 4 values below 2^30 each
+      sum[f] += (uint32_t)e[0] + (uint32_t)e[1] + (uint32_t)e[2] + (uint32_t)e[3];
+    };
+    // two fragments' lookups in flight
+    lookup(0, 0);
+#pragma unroll
+    for (int u = 0; u < NBF * NF; ++u) {
+      const int j = u / NF, f = u % NF;
+      if (u + 1 < NBF * NF) lookup((u + 1) / NF, (u + 1) % NF);
+      if (j == NB - 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sc[j][f][r] = masked(r, sc[j][f][r]);
+      }
+      add(sc[j][f], f);
+      step_end(sum[f]);
+    }
+#pragma unroll
+    for (int j = NBF; j < NB; ++j)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        int32_t e[4];
+        packed_exp(j, f, e);
+        add(e, f);
+        step_end(sum[f]);
+      }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+#pragma unroll
+      for (int o = 16; o < 64; o <<= 1) {
+        if (!FAST) {
+          const uint32_t lo = __shfl_xor((uint32_t)sum[f], o, 64);
+          const uint32_t hi = __shfl_xor((uint32_t)((uint64_t)sum[f] >> 32), o, 64);
+          sum[f] += (Sum)(((uint64_t)hi << 32) | lo);
+        } else {
+          sum[f] += __shfl_xor((uint32_t)sum[f], o, 64);
         }
       }
-      if (NARROW) sum = sum32;
-#pragma unroll
-      for (int o = LPR / 2; o > 0; o >>= 1) {
-        const uint32_t lo = __shfl_xor((uint32_t)sum, o, 64);
-        const uint32_t hi = __shfl_xor((uint32_t)(sum >> 32), o, 64);
-        sum += ((uint64_t)hi << 32) | lo;
-      }
-      const int32_t sd = a.s_d >= 0 ? a.s_d : calibrate_shift(sum, a.m_p);
-      uint64_t sr = sum >> sd;
-      sr = sr < 1 ? 1 : (sr > 0x7fffffffull ? 0x7fffffffull : sr);
-      const uint32_t F = div_2p31m1((uint32_t)sr);
-      // e F < 2^30 2^31: a shift of 61 or more leaves 0, as does 63, so
-      // the cap keeps the 64-bit shift defined (large m_p gives s_d up to 41)
-      const int32_t sh = min(32 - a.k_out + sd, 63);
-      // With sh < 32 and F < 2^sh (the usual case: F is small once s_d > 0,
-      // and S_sum >= 2^16 bounds it otherwise), Fs = F 2^(32-sh) fits in 32
-      // bits and floor(e F / 2^sh) is the high word of e Fs: one multiply.
-      // Taken when every row of the wave qualifies (a uniform branch).
-      // Either way the quotient is below 2^k_out <= 2^8 (e F < 2^(32 + s_d)
-      // when S_sum >> s_d fits S_R; smaller when S_R is clamped), so the
-      // 16-bit clamp-and-pack holds it.
-      if (__all(sh < 32 && F < (1u << (sh & 31)))) {
-        const uint32_t Fs = F << ((32 - sh) & 31);
-#pragma unroll
-        for (int j = 0; j < JW; ++j) {
-          const int32_t wd = k + j * LPR;
-          const uint32_t pw = pack_min_bytes(__umulhi(e[j][0], Fs), __umulhi(e[j][1], Fs),
-                                             __umulhi(e[j][2], Fs), __umulhi(e[j][3], Fs), pcap2);
-          if ((MASK == 2 && j < JW - 1) || MASK == 3 || wd < nword) row[wd] = pw;  // padding -> 0
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < JW; ++j) {
-          const int32_t wd = k + j * LPR;
-          uint32_t p[4];
-#pragma unroll
-          for (int b = 0; b < 4; ++b) p[b] = (uint32_t)(((uint64_t)e[j][b] * F) >> sh);
-          if ((MASK == 2 && j < JW - 1) || MASK == 3 || wd < nword)
-            row[wd] = pack_min_bytes(p[0], p[1], p[2], p[3], pcap2);  // padding -> 0
-        }
-      }
+      if (lane < 16) psum[f * 16 + lane][wave] = sum[f];
     }
   }
-  __syncthreads();
+  lds_sync();
 
-  // ---- phase 3: O = P V.  V^T is the A operand (rows = channels), P^T the
-  // B operand (columns = query rows), so a lane holds 4 consecutive channels
-  // of one query row.  Two ways to split the work over the waves:
-  //  * P3K (4 waves, rows of at least 752 keys): wave w takes the 64-key
-  //    blocks w, w + 4, ... for all 64 channels, so P is read from LDS once
-  //    per workgroup; the four partial sums of each 16-channel group are then
-  //    added through LDS (the score rows, free by then) by the wave that
-  //    owns the group (channels 16 w .. 16 w + 15);
-  //  * otherwise wave w owns channels 16 (w % 4) .. + 15 over key range
-  //    w / 4 (64-key blocks kp, kp + KP, ...), reading all of its key range
-  //    of P.
-  v4i o[NF];
+  // each row's normalization factor: lane l does row l % R, once per wave
+  uint32_t F;
+  int32_t sh;
+  {
+    const int row = lane & (R - 1);
+    uint64_t s = psum[row][0];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) o[f] = zero;
-  const int cg = P3K ? wave : (wave & 3);
-  const int32_t c0 = cg * 16;
-  if constexpr (P3K) {
-    static_assert(NW == 4, "one 16-channel group per wave");
-    v4i og[4][NF];
+    for (int w = 1; w < NW; ++w) s += psum[row][w];
+    const int32_t sd = a.s_d >= 0 ? a.s_d : calibrate_shift(s, a.m_p);
+    uint64_t sr = s >> sd;
+    sr = sr < 1 ? 1 : (sr > 0x7fffffffull ? 0x7fffffffull : sr);
+    F = div_2p31m1((uint32_t)sr);
+    // e F < 2^30 2^31: a shift of 61 or more leaves 0, as does 63, so
+    // the cap keeps the 64-bit shift defined (large m_p gives s_d up to 41)
+    sh = min(32 - a.k_out + sd, 63);
+  }
+  // With sh < 32 and F < 2^sh, Fs = F 2^(32-sh) fits in 32 bits and
+  // floor(e F / 2^sh) is the high word of e Fs: one multiply.  The row's
+  // largest value is that of ShiftExp(0) = I0 2^k_inter, which every row has;
+  // where it stays inside the output range no clamp is needed.  Otherwise the
+  // quotient is still below 2^k_out <= 2^8 (e F < 2^(32 + s_d) when
+  // S_sum >> s_d fits S_R; smaller when S_R is clamped), so the 16-bit
+  // clamp-and-pack holds it.
+  const uint32_t pcap = (1u << (a.k_out - 1)) - 1;
+  const uint32_t Fs = F << ((32 - sh) & 31);
+  const bool row_fast = FAST || (sh < 32 && F < (1u << (sh & 31)) &&
+                                 __umulhi((uint32_t)a.I0 << a.k_inter, Fs) <= pcap);
+
+  // ---- phase 3: P and O = P V.  V is the A operand (rows = channels), P the
+  // B operand (columns = query rows): a lane's bytes 4 u .. 4 u + 3 are the 4
+  // keys of slot 4 st + u it holds, in both operands.  The waves' partial
+  // sums are added through LDS.
+  const uint32_t vrow = lane * 4;  // channel lane % 16, keys 4 (lane / 16) ..
+  auto vload = [&](int j, int g) {  // of channel group g
+    const int32_t kb = j < NB - 1 ? wave + j * NW : min(wave + j * NW, nkb - 1);
+    return *(const int32_t*)(V + (kb * 1024 + g * 256) + vrow);
+  };
+  constexpr int NG = (NB + 3) / 4;  // P V steps of 4 slots (64 keys)
+  v4i vf[2][4];
+  auto vload_step = [&](int st) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        vf[st & 1][g][u] = st * 4 + u < NB ? vload(st * 4 + u, g) : 0;
+  };
+  // Every slot is packed before the first product: the words take a quarter
+  // of the exponentials' registers, which makes room for the sums.
+  v4i pw[NG][NF];
+  auto pack_all = [&](auto word) {
+#pragma unroll
+    for (int j = 0; j < NG * 4; ++j) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        if (j < NBF)
+          pw[j / 4][f][j % 4] = (int32_t)word(sc[j < NBF ? j : 0][f], f);
+        else if (j < NB) {
+          int32_t e[4];
+          packed_exp(j, f, e);
+          pw[j / 4][f][j % 4] = (int32_t)word(e, f);
+        } else {
+          pw[j / 4][f][j % 4] = 0;
+        }
+        step_end(pw[j / 4][f]);
+      }
+      if (j == (NBF - 1) / 2) vload_step(0);
+    }
+  };
+  if (FAST || __all(row_fast)) {
+    uint32_t Fr[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) Fr[f] = __shfl(Fs, f * 16 + (lane & 15), 64);
+    pack_all([&](const int32_t(&e)[4], int f) {
+      return pack_bytes(__umulhi((uint32_t)e[0], Fr[f]), __umulhi((uint32_t)e[1], Fr[f]),
+                        __umulhi((uint32_t)e[2], Fr[f]), __umulhi((uint32_t)e[3], Fr[f]));
+    });
+  } else {
+    const u16x2 pcap2 = {(unsigned short)pcap, (unsigned short)pcap};
+    uint32_t Fr[NF];
+    int32_t hr[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      Fr[f] = __shfl(F, f * 16 + (lane & 15), 64);
+      hr[f] = __shfl(sh, f * 16 + (lane & 15), 64);
+    }
+    pack_all([&](const int32_t(&e)[4], int f) {
+      uint32_t p[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[r] = (uint32_t)(((uint64_t)(uint32_t)e[r] * Fr[f]) >> hr[f]);
+      return pack_min_bytes(p[0], p[1], p[2], p[3], pcap2);
+    });
+  }
+  if (NPK > 0) lds_sync();  // the table is no longer read
+  v4i o[4][NF];
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) o[g][f] = zero;
+#pragma unroll
+  for (int st = 0; st < NG; ++st) {
+    if (st + 1 < NG) vload_step(st + 1);
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
-      for (int f = 0; f < NF; ++f) og[g][f] = zero;
-    const int8_t* vrow = Vt + (int64_t)(lane & 15) * Twp + (lane >> 4) * 16;
-    const int8_t* prow = sS + (lane & 15) * lds_row + (lane >> 4) * 16;
-    const int32_t last = Twp - 64;  // loads past the end re-read the last block
-    auto vload4 = [&](v4i(&vf)[4], int32_t j0) {
-      const int32_t jj = min(j0, last);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) vf[g] = *(const v4i*)(vrow + (int64_t)g * 16 * Twp + jj);
-    };
-    auto pv4 = [&](int32_t j0, const v4i(&vf)[4]) {
-      v4i pf[NF];
-#pragma unroll
-      for (int f = 0; f < NF; ++f) pf[f] = *(const v4i*)(prow + f * 16 * lds_row + j0);
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-          og[g][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[g], pf[f], og[g][f], 0, 0, 0);
-    };
-    // the next block's V^T fragments are in flight while this one is used
-    v4i va[4], vb[4];
-    int32_t j0 = wave * 64;
-    vload4(va, j0);
-    for (;;) {
-      if (j0 >= Twp) break;
-      vload4(vb, j0 + 4 * 64);
-      pv4(j0, va);
-      j0 += 4 * 64;
-      if (j0 >= Twp) break;
-      vload4(va, j0 + 4 * 64);
-      pv4(j0, vb);
-      j0 += 4 * 64;
-    }
-    // partial sums of the other waves' groups to LDS: [wave][g][f][lane]
-    __syncthreads();  // every wave is past its reads of P
-    v4i* part = (v4i*)sS;
-    auto publish = [&](auto G) {
-      constexpr int g = decltype(G)::value;
-      if (g != wave) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) part[((wave * 4 + g) * NF + f) * 64 + lane] = og[g][f];
-      } else {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) o[f] = og[g][f];
-      }
-    };
-    publish(IntC<0>{});
-    publish(IntC<1>{});
-    publish(IntC<2>{});
-    publish(IntC<3>{});
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      if (q == wave) continue;
-#pragma unroll
-      for (int f = 0; f < NF; ++f) o[f] += part[((q * 4 + wave) * NF + f) * 64 + lane];
-    }
-  } else {
-  const int kp = wave >> 2;
-  const int8_t* vrow = Vt + (int64_t)(c0 + (lane & 15)) * Twp + (lane >> 4) * 16;
-  const int8_t* prow = sS + (lane & 15) * lds_row + (lane >> 4) * 16;
-  const int32_t last = Twp - 64;  // loads past the end re-read the last block
-  auto vload = [&](int32_t j0) { return *(const v4i*)(vrow + min(j0, last)); };
-  auto pv = [&](int32_t j0, const v4i& vf) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      const v4i pf = *(const v4i*)(prow + f * 16 * lds_row + j0);
-      o[f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf, pf, o[f], 0, 0, 0);
-    }
-  };
-  // four V^T fragments in flight, as for the keys
-  constexpr int32_t SJ = 64 * KP;  // key stride of one wave
-  const int32_t j00 = kp * 64;
-  v4i v0 = vload(j00), v1 = vload(j00 + SJ), v2 = vload(j00 + 2 * SJ), v3 = vload(j00 + 3 * SJ);
-  for (int32_t j0 = j00; j0 < Twp; j0 += 4 * SJ) {
-    pv(j0, v0);
-    v0 = vload(j0 + 4 * SJ);
-    if (j0 + SJ >= Twp) break;
-    pv(j0 + SJ, v1);
-    v1 = vload(j0 + 5 * SJ);
-    if (j0 + 2 * SJ >= Twp) break;
-    pv(j0 + 2 * SJ, v2);
-    v2 = vload(j0 + 6 * SJ);
-    if (j0 + 3 * SJ >= Twp) break;
-    pv(j0 + 3 * SJ, v3);
-    v3 = vload(j0 + 7 * SJ);
+      for (int f = 0; f < NF; ++f)
+        o[g][f] = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf[st & 1][g], pw[st][f], o[g][f], 0, 0, 0);
+    step_end();
   }
-  if (KP > 1) {
-    // add the partial sums of the other key ranges into the kp = 0 waves
-    if (kp > 0) {
+  v4i* part = (v4i*)sbuf;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) ored[(((kp - 1) * 4 + cg) * NF + f) * 64 + lane] = o[f];
-    }
-    __syncthreads();
-    if (kp > 0) return;
+  for (int g = 0; g < 4; ++g)
 #pragma unroll
-    for (int q = 0; q < KP - 1; ++q)
+    for (int f = 0; f < NF; ++f) part[((wave * 4 + g) * NF + f) * 64 + lane] = o[g][f];
+  lds_sync();
+
+  const uint32_t bw = slice / (uint32_t)a.H;  // image * nW + window
+  const int32_t h = (int32_t)(slice - bw * (uint32_t)a.H);
+  const int32_t b_img = (int32_t)(bw / (uint32_t)a.nW), w = (int32_t)(bw - (uint32_t)b_img * a.nW);
+  const int32_t wy = w / a.nwx, wx = w - wy * a.nwx;
+  int8_t* const out = a.out + ((int64_t)b_img * a.T + wy * a.win_h * a.grid_w + wx * a.win_w) * a.D +
+                      h * a.hd;
+  const int64_t rnd = (int64_t)1 << (a.pv_shift - 1);
+  // tile t (channel group t / NF, fragment t % NF): a lane holds 4 channels of
+  // one token
 #pragma unroll
-      for (int f = 0; f < NF; ++f) {
-        const v4i t = ored[((q * 4 + cg) * NF + f) * 64 + lane];
-        o[f] += t;
-      }
-  }
-  }
-  const int32_t b_img = bw / a.nW, w = bw % a.nW;
-  const int32_t wy = w / a.nwx, wx = w % a.nwx;
-  const int32_t c = c0 + (lane >> 4) * 4;
-  if (c0 >= a.hd) return;  // channel group past the head dimension
+  for (int t0 = 0; t0 < 4 * NF; t0 += NW) {
+    const int t = t0 + wave, g = t / NF, f = t % NF;
+    if (t >= 4 * NF || g * 16 >= a.hd) break;  // channel group past the head dimension
+    v4i s = part[t * 64 + lane];
 #pragma unroll
-  for (int f = 0; f < NF; ++f) {
+    for (int q = 1; q < NW; ++q) s += part[(q * 4 * NF + t) * 64 + lane];
     const int32_t i = i0 + f * 16 + (lane & 15);
     if (i >= Tw) continue;
-    const int32_t t = (wy * a.win_h + i / a.win_w) * a.grid_w + wx * a.win_w + i % a.win_w;
-    uint32_t packed = 0;
+    const int32_t iy = fdiv(i, a.win_w, a.inv_ww);
+    const int32_t tok = iy * (a.grid_w - a.win_w) + i;
+    int32_t v[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      packed |= (uint32_t)(rq(o[f][r], a.pv_mult, a.pv_shift) & 0xff) << (8 * r);
-    *(uint32_t*)(a.out + ((int64_t)b_img * a.T + t) * a.D + h * a.hd + c) = packed;
+    for (int r = 0; r < 4; ++r) {
+      const int32_t acc = min(max(s[r], -a.pv_clamp), a.pv_clamp);
+      v[r] = min(max((int32_t)(((int64_t)acc * a.pv_mult + rnd) >> a.pv_shift), kQmin), kQmax);
+    }
+    *(uint32_t*)(out + (int64_t)tok * a.D + (g * 16 + (lane >> 4) * 4)) =
+        pack_bytes((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
   }
 }
 
-// [B, T, 3D] token-major QKV -> window-major Q, K and V^T.  One thread per
-// 16-byte chunk of a token's 3D channels.
-__global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, int32_t B,
-                                                           QkvLayout L) {
-  const int32_t chunks = 3 * L.D / 16;
-  const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (g >= (int64_t)B * L.T * chunks) return;
-  const int64_t m = g / chunks;
-  const int32_t n = (int32_t)(g % chunks) * 16;
-  const int32_t b = (int32_t)(m / L.T), t = (int32_t)(m % L.T);
-  const int32_t ty = t / L.grid_w, tx = t % L.grid_w;
-  const int32_t w = (ty / L.win_h) * L.nwx + tx / L.win_w;
-  const int32_t li = (ty % L.win_h) * L.win_w + tx % L.win_w;
-  const int32_t part = n / L.D, rem_n = n % L.D;
-  const int32_t h = rem_n >> L.hs, c = rem_n & ((1 << L.hs) - 1);
-  const int64_t slice = ((int64_t)b * L.nW + w) * L.H + h;
-  const v4i v = *(const v4i*)(qkv + m * 3 * L.D + n);
-  if (part < 2) {
-    *(v4i*)((part == 0 ? L.q : L.k) + (slice * L.Tw + li) * 64 + c) = v;
-  } else {
-    int8_t* dst = L.vt + (slice * 64 + c) * L.Twp + li;
-    const int8_t* bytes = (const int8_t*)&v;
+// [B, T, 3D] token-major QKV -> window-major Q, K and V (see QkvLayout).
+// One thread per 16-byte chunk of Q and K; the values go in groups of 4
+// consecutive keys: a thread loads a 16-channel chunk of each and stores 4
+// keys of a channel per word (byte stores of single keys made this 16.7 us
+// against 7.0 at 4 x 1600 tokens of 384 channels).  n_qk and n_v are the two
+// parts' thread counts.
+__global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, QkvLayout L,
+                                                           uint32_t n_qk, uint32_t n_v) {
+  const uint32_t g = blockIdx.x * 256u + threadIdx.x;
+  if (g < n_qk) {
+    const uint32_t chunks = 2 * L.D / 16;
+    const uint32_t m = g / chunks;
+    const int32_t n = (int32_t)(g - m * chunks) * 16;
+    const int32_t b = (int32_t)(m / (uint32_t)L.T), t = (int32_t)(m - (uint32_t)b * L.T);
+    const int32_t ty = t / L.grid_w, tx = t - ty * L.grid_w;
+    const int32_t wy = ty / L.win_h, wx = tx / L.win_w;
+    const int32_t li = (ty - wy * L.win_h) * L.win_w + tx - wx * L.win_w;
+    const int32_t part = n >= L.D, rem_n = n - part * L.D;
+    const int32_t h = rem_n >> L.hs, c = rem_n & ((1 << L.hs) - 1);
+    const int64_t slice = ((int64_t)b * L.nW + wy * L.nwx + wx) * L.H + h;
+    *(v4i*)((part == 0 ? L.q : L.k) + (slice * L.Tw + li) * 64 + c) =
+        *(const v4i*)(qkv + (int64_t)m * 3 * L.D + n);
+    return;
+  }
+  const uint32_t v = g - n_qk;
+  if (v >= n_v) return;
+  // (window, key group, channel chunk), the chunks fastest
+  const uint32_t chunks = L.D / 16, groups = (L.Tw + 3) / 4;
+  const uint32_t kc = v / chunks, bw = kc / groups;
+  const int32_t n = (int32_t)(v - kc * chunks) * 16, k0 = (int32_t)(kc - bw * groups) * 4;
+  const int32_t b = (int32_t)(bw / (uint32_t)L.nW), w = (int32_t)(bw - (uint32_t)b * L.nW);
+  const int32_t wy = w / L.nwx, wx = w - wy * L.nwx;
+  v4i x[4];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dst[(int64_t)r * L.Twp] = bytes[r];
+  for (int r = 0; r < 4; ++r) {
+    const int32_t li = min(k0 + r, L.Tw - 1);  // keys past the window carry no weight
+    const int32_t iy = li / L.win_w;
+    const int64_t m = (int64_t)b * L.T + (wy * L.win_h + iy) * L.grid_w + wx * L.win_w + li -
+                      iy * L.win_w;
+    x[r] = *(const v4i*)(qkv + m * 3 * L.D + 2 * L.D + n);
+  }
+  const int32_t h = n >> L.hs, c = n & ((1 << L.hs) - 1);
+  int8_t* dst = L.vt + ((int64_t)bw * L.H + h) * 64 * L.Twp + vt_key(k0) + vt_channel(c);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    // 4 keys x 4 channels transposed
+    const uint32_t p01 = __builtin_amdgcn_perm((uint32_t)x[1][q], (uint32_t)x[0][q], 0x05010400u);
+    const uint32_t p23 = __builtin_amdgcn_perm((uint32_t)x[3][q], (uint32_t)x[2][q], 0x05010400u);
+    const uint32_t q01 = __builtin_amdgcn_perm((uint32_t)x[1][q], (uint32_t)x[0][q], 0x07030602u);
+    const uint32_t q23 = __builtin_amdgcn_perm((uint32_t)x[3][q], (uint32_t)x[2][q], 0x07030602u);
+    *(uint32_t*)(dst + vt_channel(4 * q + 0)) = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+    *(uint32_t*)(dst + vt_channel(4 * q + 1)) = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+    *(uint32_t*)(dst + vt_channel(4 * q + 2)) = __builtin_amdgcn_perm(q23, q01, 0x05040100u);
+    *(uint32_t*)(dst + vt_channel(4 * q + 3)) = __builtin_amdgcn_perm(q23, q01, 0x07060302u);
   }
 }
 
-// Dynamic LDS above 64 KB must be allowed per kernel; the attribute is set
-// once per (device, kernel) and size high-water mark, under a lock so that
-// threads launching on several devices at once all see it set.
-hipError_t allow_dynamic_lds(const void* kern, size_t smem) {
-  static std::mutex mu;
-  static std::map<std::pair<int, const void*>, size_t> done;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  std::lock_guard<std::mutex> lk(mu);
-  size_t& have = done[{dev, kern}];
-  if (smem <= have) return hipSuccess;
-  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e == hipSuccess) have = smem;
-  return e;
-}
-
-template <int R, int LPR, bool NARROW, int MASK, int NW, int JW, bool P3K>
-hipError_t launch_variant(const AttnArgs& a, int32_t clampL, hipStream_t s) {
-  const int32_t lds_row = a.Twp + 16;
-  const size_t smem = (size_t)R * lds_row;
-  // the split-key P V exchange needs 16 KB per 16 query rows of score rows
-  if (P3K && lds_row < 1024) return hipErrorInvalidValue;
-  auto kern = attention_kernel<R, LPR, NARROW, MASK, NW, JW, P3K>;
-  if (smem > 65536) {
-    const hipError_t e = allow_dynamic_lds((const void*)kern, smem);
-    if (e != hipSuccess) return e;
-  }
-  const int32_t nrb = (a.Tw + R - 1) / R;
-  const int64_t ntiles = (int64_t)nrb * a.H * a.B * a.nW;
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntiles), dim3(64 * NW), smem, s, a, lds_row, clampL,
+template <int R, int NW, int NB, bool FAST>
+hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
+  const uint32_t nrb = (uint32_t)(a.Tw + R - 1) / R;
+  const uint32_t ntiles = nrb * (uint32_t)(a.H * a.B * a.nW);
+  hipLaunchKernelGGL((attention_kernel<R, NW, NB, FAST>), dim3(ntiles), dim3(64 * NW), 0, s, a,
                      nrb, ntiles);
   return hipGetLastError();
 }
 
-template <int R, int LPR, int NW, int JW = 8, bool P3K = false>
-hipError_t launch_rows(const AttnArgs& a, int32_t clampL, int64_t emax, hipStream_t s) {
-  // A lane sums at most 4 JW ShiftExp values, each at most emax = ShiftExp(0)
-  // = I0 * 2^k_inter: 32-bit partial sums are exact while 4 JW emax < 2^32.
-  const bool narrow = emax * 4 * JW < ((int64_t)1 << 32);
-  int mask = (a.Tw & 3) ? 1 : (a.Tw == a.Twp && (JW - 1) * LPR <= (a.Twp >> 2) ? 2 : 0);
-  // exact fit: mask only the last two word steps (the 400-token windows, 3%)
-  if (mask == 0 && JW * LPR == (a.Twp >> 2) && (JW - 2) * LPR <= (a.Tw >> 2)) mask = 3;
-  if (narrow) {
-    if (mask == 3) return launch_variant<R, LPR, true, 3, NW, JW, P3K>(a, clampL, s);
-    if (mask == 2) return launch_variant<R, LPR, true, 2, NW, JW, P3K>(a, clampL, s);
-    return mask ? launch_variant<R, LPR, true, 1, NW, JW, P3K>(a, clampL, s)
-                : launch_variant<R, LPR, true, 0, NW, JW, P3K>(a, clampL, s);
+// The instance with nb slots, LO <= nb <= HI.
+template <int R, int NW, int LO, int HI>
+hipError_t launch_slots(const AttnArgs& a, int32_t nb, bool fast, hipStream_t s) {
+  if constexpr (LO < HI) {
+    if (nb > LO) return launch_slots<R, NW, LO + 1, HI>(a, nb, fast, s);
   }
-  if (mask == 3) return launch_variant<R, LPR, false, 3, NW, JW, P3K>(a, clampL, s);
-  if (mask == 2) return launch_variant<R, LPR, false, 2, NW, JW, P3K>(a, clampL, s);
-  return mask ? launch_variant<R, LPR, false, 1, NW, JW, P3K>(a, clampL, s)
-              : launch_variant<R, LPR, false, 0, NW, JW, P3K>(a, clampL, s);
+  // 32-bit sums over a wave's keys are exact while 16 nb ShiftExp(0) < 2^32
+  return fast && (((int64_t)a.I0 << a.k_inter) * 16 * LO < ((int64_t)1 << 32))
+             ? launch_variant<R, NW, LO, true>(a, s)
+             : launch_variant<R, NW, LO, false>(a, s);
 }
 
-// The 16-word variants with the smallest word count the window needs: 13
-// words cover 1600-token rows over 32 lanes, 14 rows of up to 1792 bytes
-// over 32 lanes, 10 the 320-byte padded 300-query rows.
-template <int R, int LPR, int NW, bool P3K = false>
-hipError_t launch_fit16(const AttnArgs& a, int32_t clampL, int64_t emax, hipStream_t s) {
-  const int32_t jw = ((a.Twp >> 2) + LPR - 1) / LPR;
-  if (jw <= 10) return launch_rows<R, LPR, NW, 10, P3K>(a, clampL, emax, s);
-  if (jw <= 13) return launch_rows<R, LPR, NW, 13, P3K>(a, clampL, emax, s);
-  if (jw == 14) return launch_rows<R, LPR, NW, 14, P3K>(a, clampL, emax, s);
-  return launch_rows<R, LPR, NW, 16, P3K>(a, clampL, emax, s);
+// Whether P = floor(e F / 2^sh) is one high-word multiply for every row of n
+// keys, and inside the output range without a clamp.  With E = ShiftExp(0) the
+// sum S lies in [E, n E], sh = 32 - k_out + s_d, F = floor((2^31 - 1) / S_R).
+//  * s_d < k_out gives sh < 32.
+//  * S_R >= 2^(k_out - s_d) gives F < 2^(31 - k_out + s_d) = 2^(sh - 1).
+//  * Static s_d <= k_inter: E is a multiple of 2^s_d, so S_R >= E / 2^s_d (or
+//    S_R is 2^31 - 1) and E F < 2^31 2^s_d = 2^(sh + k_out - 1), the limit.
+//  * Dynamic s_d > 0 has S > 2^(31 - m_p) and S_R >= 2^(30 - m_p); with
+//    E <= 2^(30 - m_p) other keys make up half of S, and E F stays below the
+//    limit by nearly a factor of two.  s_d = 0 is the static case.
+bool p_fast(const AttnArgs& a, int64_t n) {
+  const int64_t E = (int64_t)a.I0 << a.k_inter;
+  if (a.s_d >= 0)
+    return a.s_d < a.k_out && a.s_d <= a.k_inter && (E >> a.s_d) >= ((int64_t)1 << a.k_out);
+  // the largest s_d: bit length of n E - 1, + m_p - 31
+  const int32_t bits = 64 - __builtin_clzll((unsigned long long)(n * E));
+  return bits + a.m_p - 31 < a.k_out && E >= ((int64_t)1 << a.k_out) &&
+         a.m_p + a.k_out <= 30 && E <= ((int64_t)1 << (30 - a.m_p));
 }
 
-template <int R>
-hipError_t launch_lpr(const AttnArgs& a, int32_t clampL, int64_t emax, int64_t wgs,
-                      hipStream_t s) {
-  // Rows per wave: a lane holds JW words (4 JW scores) of its row, and the
-  // LPR lanes of a row combine their sums in log2(LPR) shuffle steps.  With
-  // 32-row blocks each wave normalizes 8 rows; doing them 4 or 8 (windows)
-  // or 2 (long rows) at a time overlaps the rows' serial sum-shuffle-divide
-  // chains (measured against one row group of 16 or 64 lanes).
-  if (a.Twp <= 512) {
-    // 7 words over 16 lanes fit the 448-byte padded 400-token rows exactly;
-    // in 32-row blocks that variant needs 60 VGPRs against 95 for 8 lanes of
-    // 14 words (two row groups per wave instead of one), which fits more
-    // workgroups per CU: the medium encoder 3.9% faster
-    if constexpr (R == 32) {
-      if ((a.Twp >> 2) <= 7 * 16) return launch_rows<32, 16, 4, 7>(a, clampL, emax, s);
-      return launch_fit16<32, 8, 4>(a, clampL, emax, s);
-    }
-    if ((a.Twp >> 2) <= 7 * 16) return launch_rows<R, 16, 4, 7>(a, clampL, emax, s);
-    return launch_rows<R, 16, 4>(a, clampL, emax, s);
-  }
-  if (a.Twp <= 1024) return launch_rows<R, 32, 4>(a, clampL, emax, s);
-  // Long rows: small grids spread a 32-row block over 16 waves so that every
-  // SIMD holds several, each wave normalizing its 2 rows together (measured
-  // best of 16 or 32 rows over 4, 8 or 16 waves for 1600-token rows at
-  // batch 1).
-  if (wgs * 4 <= 2048) return launch_fit16<32, 32, 16>(a, clampL, emax, s);
-  // (P V split by key blocks over the 4 waves: P read from LDS once)
-  if constexpr (R == 32) {
-    // Padded rows of more than 1408 and at most 1600 bytes with 32-bit lane
-    // sums: 16 lanes per row,
-    // 25 words each, so a wave normalizes 4 rows at a time and the per-row
-    // work (sum shuffles, shift calibration, reciprocal) is shared by twice
-    // the scores: 130 VGPRs, global attention of the 384-wide encoder 5%
-    // faster than 32 lanes of 13 words.  (With 64-bit lane sums the
-    // variant needs over 200 VGPRs.)
-    const int32_t words = a.Twp >> 2;
-    if (words > 22 * 16 && words <= 25 * 16 && emax * 4 * 25 < ((int64_t)1 << 32))
-      return launch_rows<32, 16, 4, 25, true>(a, clampL, emax, s);
-    return launch_fit16<32, 32, 4, true>(a, clampL, emax, s);
-  }
-  return launch_rows<R, 64, 4>(a, clampL, emax, s);
+// Accumulator clamp of a requantization by m / 2^s: beyond |acc| = L the
+// result saturates (|acc m| >= 129 2^s), and L m / 2^s stays far inside int32.
+// (No accumulator here reaches 2^30.)
+int32_t clamp_bound(int64_t am, int32_t shift) {
+  if (shift > 54 || am == 0) return 1 << 30;
+  const int64_t L = 129 * ((int64_t)1 << shift) / am + 1;
+  return L > (1 << 30) ? 1 << 30 : (int32_t)L;
 }
 
 }  // namespace
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.B == 0) return hipSuccess;
-  // Accumulator clamp for the score requantization: beyond |acc| = L the
-  // result saturates (|acc * mult| >= 129 * 2^shift) and the product of the
-  // clamped value stays far inside 64 bits.
-  const int64_t am = a.score_mult < 0 ? -(int64_t)a.score_mult : (int64_t)a.score_mult;
-  int64_t L = am == 0 ? 1 : (129 * ((int64_t)1 << a.score_shift)) / am + 1;
-  if (L > ((int64_t)1 << 30)) L = (int64_t)1 << 30;
-  const int64_t emax = (int64_t)a.I0 << a.k_inter;  // ShiftExp(0), the largest value
-  // The unclamped score form: |acc| <= 2^20 keeps the 64-bit value below
-  // 2^62 for s <= 54, and the shifted value (below 2^51 / 2^s + 129) inside
-  // int32 for s >= 32, or for smaller s when |m| 2^20 / 2^s is small enough.
   AttnArgs b = a;
-  b.rq_fast = a.score_shift <= 54 &&
-              (a.score_shift >= 32 || ((am << 20) >> a.score_shift) + 257 < ((int64_t)1 << 31));
-  // Fill the chip: fall back to 16-row blocks when 32-row blocks would give
-  // fewer than two workgroups per CU.
+  // A score multiplier with room to spare takes a larger shift (the same
+  // value m / 2^s, so the same rounding), which reaches the high-word form.
+  int64_t am = a.score_mult < 0 ? -(int64_t)a.score_mult : (int64_t)a.score_mult;
+  while (b.score_shift < 32 && am < ((int64_t)1 << 30)) {
+    b.score_mult *= 2;
+    b.score_shift += 1;
+    am *= 2;
+  }
+  b.score_clamp = clamp_bound(am, b.score_shift);
+  b.pv_clamp = clamp_bound(a.pv_mult < 0 ? -(int64_t)a.pv_mult : (int64_t)a.pv_mult, a.pv_shift);
+  b.rq_fast = b.score_shift >= 32 && b.score_shift <= 54;
+  b.inv_ww = 1.0f / (float)a.win_w;
+  // floor(z / I0) = umulhi(z, ceil(2^32 / I0)) for z <= k_inter I0 <= 16 I0:
+  // the excess z (I0 ceil(2^32 / I0) - 2^32) < 16 I0^2 <= 2^32
+  b.inv_I0 = a.I0 == 1 ? 0 : (uint32_t)((((uint64_t)1 << 32) + a.I0 - 1) / (uint32_t)a.I0);
+  const bool fast = b.rq_fast && p_fast(a, a.Tw);
+  const int32_t nkb = (a.Tw + 15) >> 4;  // 16-key blocks
   const int64_t wg32 = (int64_t)((a.Tw + 31) / 32) * a.H * a.B * a.nW;
-  const int64_t wg16 = (int64_t)((a.Tw + 15) / 16) * a.H * a.B * a.nW;
-  if (wg32 < 512) return launch_lpr<16>(b, (int32_t)L, emax, wg16, s);
-  return launch_lpr<32>(b, (int32_t)L, emax, wg32, s);
+  if (nkb <= 32) {
+    // up to 512 keys: 4 waves, in 16-row blocks where 32-row blocks would
+    // give fewer than two workgroups per CU (2 waves of twice the slots: the
+    // medium encoder 1% slower)
+    return wg32 < 512 ? launch_slots<16, 4, 1, 8>(b, (nkb + 3) / 4, fast, s)
+                      : launch_slots<32, 4, 1, 8>(b, (nkb + 3) / 4, fast, s);
+  }
+  // Longer rows: 8 waves, two workgroups per CU, which fill each other's
+  // barriers (16 waves, one workgroup: 53 against 40 us at 4 x 6 heads of
+  // 1600 keys); grids of at most one workgroup per CU spread over 16 waves.
+  if (wg32 <= 256) return launch_slots<32, 16, 3, 8>(b, (nkb + 15) / 16, fast, s);
+  return launch_slots<32, 8, 5, 16>(b, (nkb + 7) / 8, fast, s);
 }
 
 hipError_t launch_qkv_relayout(const int8_t* qkv, int32_t B, const QkvLayout& L,
                                hipStream_t s) {
-  const int64_t n = (int64_t)B * L.T * (3 * L.D / 16);
-  if (n == 0) return hipSuccess;
-  dim3 grid((unsigned)((n + 255) / 256)), block(256);
-  hipLaunchKernelGGL(qkv_relayout_kernel, grid, block, 0, s, qkv, B, L);
+  // batch * tokens < 2^23 and dim <= 16384 keep the counts below 2^32
+  const int64_t n_qk = (int64_t)B * L.T * (2 * L.D / 16);
+  const int64_t n_v = (int64_t)B * L.nW * ((L.Tw + 3) / 4) * (L.D / 16);
+  if (n_qk == 0) return hipSuccess;
+  if (n_qk + n_v + 255 >= ((int64_t)1 << 32)) return hipErrorInvalidValue;
+  dim3 grid((unsigned)((n_qk + n_v + 255) / 256)), block(256);
+  hipLaunchKernelGGL(qkv_relayout_kernel, grid, block, 0, s, qkv, L, (uint32_t)n_qk,
+                     (uint32_t)n_v);
   return hipGetLastError();
 }
 

@@ -8,7 +8,7 @@
 //   h  = LN1'(y);  q, k, v^T = rq(h Wq'^T + bq')        -> HBM, window-major,
 //                                                          for the next block
 //
-// Only att and x are read and only y (and the next block's Q, K, V^T) are
+// Only att and x are read and only y (and the next block's Q, K, V) are
 // written: x1, h2, g and h live in registers and LDS.  Every weight byte is
 // used by exactly one wave of the workgroup (the slab is one 16-token MFMA
 // tile), so weights are loaded from global memory straight into MFMA A
@@ -115,7 +115,7 @@ __device__ __forceinline__ uint32_t slab_layernorm(uint32_t xw, int w, int lane,
 }
 
 // Window-major offsets of token m (a valid token) for the next attention:
-// its row of Q and K, and its column of V^T.
+// its row of Q and K, and its column of V.
 __device__ __forceinline__ void qkv_dest(const TailArgs& a, int64_t m, int64_t& tq, int64_t& tv) {
   const QkvLayout& Lq = a.qkv;
   const int32_t b = fdiv((int32_t)m, Lq.T, a.inv_T);
@@ -126,7 +126,7 @@ __device__ __forceinline__ void qkv_dest(const TailArgs& a, int64_t m, int64_t& 
   const int64_t bw = (int64_t)b * Lq.nW + wy * Lq.nwx + wx;
   const int32_t li = iy * Lq.win_w + ix;
   tq = (bw * Lq.H * Lq.Tw + li) * 64;
-  tv = bw * Lq.H * 64 * Lq.Twp + li;
+  tv = bw * Lq.H * 64 * Lq.Twp + vt_key(li);
 }
 
 // QKV of the slab from h in bufX (wave w: channels 48w .. 48w + 47, weights
@@ -160,9 +160,9 @@ __device__ __forceinline__ void slab_qkv(const TailArgs& a, const v4i (&wq)[3][D
       int8_t* base = part == 0 ? Lq.q : Lq.k;
       *(uint32_t*)(base + tq + (int64_t)h * Lq.Tw * 64 + c) = pack4(v[0], v[1], v[2], v[3]);
     } else {
-      int8_t* dst = Lq.vt + tv + ((int64_t)h * 64 + c) * Lq.Twp;
+      int8_t* dst = Lq.vt + tv + (int64_t)h * 64 * Lq.Twp + vt_channel(c);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) dst[(int64_t)r * Lq.Twp] = (int8_t)v[r];
+      for (int r = 0; r < 4; ++r) dst[vt_channel(r)] = (int8_t)v[r];
     }
   }
 }
@@ -268,7 +268,7 @@ __global__ __launch_bounds__(64 * NWV) void block_tail_kernel(TailArgs a) {
   }
   for (int t = tid; t < 256; t += 64 * NWV)
     glut[t] = (int8_t)rq(sd_gelu(t - 128, a.g_I0, a.g_kinter, a.g_kout), a.g_mult, a.g_shift);
-  // window-major destination of the lane's token for the next block's Q, K, V^T
+  // window-major destination of the lane's token for the next block's Q, K, V
   int64_t tq = 0, tv = 0;
   if (NEXT && tok_ok) qkv_dest(a, m, tq, tv);
   if (tid < TS * D / 16) *(v4i*)(bufX + ar * XS + ac * 16) = att_chunk;
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(64 * NWV) void block_tail_kernel(TailArgs a) {
   slab_qkv(a, wq, bufX, chan + NQKV, w, tl, cq, kq, tok_ok, tq, tv);
 }
 
-// The first block's h = LN1(x) and Q, K, V^T = rq(h Wq^T + bq), scattered
+// The first block's h = LN1(x) and Q, K, V = rq(h Wq^T + bq), scattered
 // window-major, for one 16-token slab per workgroup: the tail kernel's last
 // stage applied to the encoder input, so the first block needs no separate
 // LayerNorm and QKV launches.  Same wave layout: wave w normalizes channels

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
   constexpr bool STAGED = !LAT && (EPI == EPI_STORE || EPI == EPI_GELU);
   constexpr bool RSTAGED = !LAT && RES;  // residual outputs (and LayerNorm's) likewise
   // QKV: the Q and K words likewise (a 16-channel chunk of a token lies in
-  // one head's 64-byte window-major row); V^T keeps its byte scatter
+  // one head's 64-byte window-major row); V keeps its byte scatter
   constexpr bool QSTAGED = !LAT && EPI == EPI_QKV;
   // Tiles inside M x N take an epilogue without per-lane validity tests in
   // the 384-channel LayerNorm tile (one workgroup per CU) and in the staged
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
   auto sX = [&](int buf) { return sbuf + (2 * TN + buf * TM) * LROW; };
   __shared__ int8_t glut[EPI == EPI_GELU ? 256 : 1];
   __shared__ RqI64 rqc[TN];                         // output requantization per channel
-  __shared__ int64_t qoff[EPI == EPI_QKV ? TM : 1][2];  // QKV: Q/K and V^T offsets per token
+  __shared__ int64_t qoff[EPI == EPI_QKV ? TM : 1][2];  // QKV: Q/K and V offsets per token
   __shared__ RqI64 lnq[LN ? TN : 1];  // LayerNorm output requantization per channel
   // per-wave row sums of the LayerNorm epilogue: in the first weight tile,
   // free once the K loop's last barrier has passed
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
     ch_ok[i] = nch[i] < N;  // N is a multiple of 16: the 4 channels are all valid
   }
   int64_t tok[FJ];   // per token: output row (STORE/GELU/RESID) or Q/K offset (QKV)
-  int64_t tokv[FJ];  // QKV: V^T offset of the token
+  int64_t tokv[FJ];  // QKV: V offset of the token
   int64_t rtok[FJ];  // RESID: row of the skip input (PATCH: of the positional table)
   bool tok_ok[FJ];
 #pragma unroll
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
       const int64_t bw = (int64_t)b * Lq.nW + wy * Lq.nwx + wx;
       const int32_t li = iy * Lq.win_w + ix;
       qoff[t][0] = (bw * Lq.H * Lq.Tw + li) * 64;
-      qoff[t][1] = bw * Lq.H * 64 * Lq.Twp + li;
+      qoff[t][1] = bw * Lq.H * 64 * Lq.Twp + vt_key(li);
     }
   }
   if (LN) {
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
         is_v = part == 2;
         qk_base = part == 0 ? Lq.q : Lq.k;
         ch_qk = (int64_t)h * Lq.Tw * 64 + c;
-        ch_v = ((int64_t)h * 64 + c) * Lq.Twp;
+        ch_v = (int64_t)h * 64 * Lq.Twp + vt_channel(c);
       }
 #pragma unroll
       for (int j = 0; j < FJ; ++j) {
@@ -423,14 +423,14 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, int32
           const uint32_t word = pack4(o[0], o[1], o[2], o[3]);
           if (!RSTAGED) *(uint32_t*)(a.y + tok[j] + n) = word;
           if (LN || RSTAGED) xw[i][j] = word;
-        } else {  // EPI_QKV: scatter into window-major Q, K and V^T
+        } else {  // EPI_QKV: scatter into window-major Q, K and V
           if (!is_v) {
             if (QSTAGED) xw[i][j] = pack4(u[0], u[1], u[2], u[3]);
             else *(uint32_t*)(qk_base + tok[j] + ch_qk) = pack4(u[0], u[1], u[2], u[3]);
           } else {
             int8_t* dst = a.qkv.vt + tokv[j] + ch_v;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) dst[(int64_t)r * a.qkv.Twp] = (int8_t)u[r];
+            for (int r = 0; r < 4; ++r) dst[vt_channel(r)] = (int8_t)u[r];
           }
         }
       }

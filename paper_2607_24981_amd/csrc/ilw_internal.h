@@ -235,10 +235,10 @@ __device__ __forceinline__ uint32_t div_2p31m1(uint32_t s) {
   const double sd = (double)s;
   double r = __builtin_amdgcn_rcp(sd);
   r = fma(r, fma(-sd, r, 1.0), r);
-  int64_t q = (int64_t)(2147483647.0 * r);
-  const int64_t rem = 2147483647LL - q * (int64_t)s;
+  uint32_t q = (uint32_t)(2147483647.0 * r);  // at most 2^31
+  const int64_t rem = 2147483647LL - (int64_t)((uint64_t)q * s);
   q += rem < 0 ? -1 : (rem >= (int64_t)s ? 1 : 0);
-  return (uint32_t)q;
+  return q;
 }
 
 // Per-channel output constants: beta, multiplier, shift and the saturation
@@ -373,22 +373,29 @@ enum GemmEpilogue {
   EPI_STORE = 0,     // y = rq(acc)
   EPI_GELU = 1,      // y = table[rq(acc)] (SD-ShiftGELU + its requantization)
   EPI_RESID = 2,     // y = Res(rq(acc), resid)
-  EPI_QKV = 3,       // scatter rq(acc) into window-major Q, K, V^T
+  EPI_QKV = 3,       // scatter rq(acc) into window-major Q, K, V
   EPI_RESID_LN = 4,  // EPI_RESID, and y2 = LayerNorm(y) (the tile holds whole rows)
   EPI_PATCH = 5      // patch embedding: x gathered from an image, y = Res(rq(acc), pos)
 };
 
-// Window-major Q, K, V^T buffers used by the attention kernel:
-//   Q, K [B, nW, H, Tw, 64],  V^T [B, nW, H, 64, Twp]  (Twp = Tw rounded to 64)
-// Window-major Q, K [B, nW, H, Tw, 64] and V^T [B, nW, H, 64, Twp]: rows of
-// 64 bytes per head whatever the head dimension (2^hs, 32 or 64); the bytes
-// past the head dimension are never written and never used.
+// Window-major Q, K [B, nW, H, Tw, 64] and V [B, nW, H, Twp / 16, 4, 4, 16, 4]
+// (Twp = Tw rounded to 64): Q and K rows of 64 bytes per head; V in blocks of
+// 16 keys as [channel / 16][key / 4][channel % 16][key % 4], so that an
+// attention wave's load of 4 keys per lane is 256 consecutive bytes.  64 channels per head whatever the head dimension (2^hs,
+// 32 or 64); the bytes past the head dimension are never written and never
+// used, and those of keys past the window carry no weight.
 struct QkvLayout {
   int8_t* q;
   int8_t* k;
   int8_t* vt;
   int32_t T, D, H, grid_w, win_h, win_w, nwx, nW, Tw, Twp, hs;
 };
+
+// Offset of key k, and of channel c, in a (window, head)'s V.
+__device__ __forceinline__ int32_t vt_key(int32_t k) {
+  return (k >> 4) * 1024 + ((k >> 2) & 3) * 64 + (k & 3);
+}
+__device__ __forceinline__ int32_t vt_channel(int32_t c) { return (c >> 4) * 256 + (c & 15) * 4; }
 
 struct GemmArgs {
   const int8_t* x;   // [M, K] activations
@@ -486,7 +493,7 @@ struct TailArgs {
   float inv_T, inv_gw, inv_wh, inv_ww;
 };
 hipError_t launch_block_tail(const TailArgs& a, hipStream_t s);
-// h = LN1(x) and the window-major Q, K, V^T of the first block (dim 192), from
+// h = LN1(x) and the window-major Q, K, V of the first block (dim 192), from
 // TailArgs' x, M, LN1, QKV and layout fields.
 hipError_t launch_block_head(const TailArgs& a, hipStream_t s);
 
@@ -519,7 +526,11 @@ struct AttnArgs {
   int32_t B, T, D, H, grid_w, win_h, win_w, nwx, nW, Tw, Twp;
   int32_t score_mult, score_shift, I0, k_inter, k_out, m_p, s_d, pv_mult, pv_shift;
   int32_t hd;        // head dimension: 32 or 64
-  int32_t rq_fast;   // set by launch_attention: the score shift cannot overflow int32
+  // set by launch_attention: the scores take the high-word form, accumulator
+  // clamps of the two requantizations, reciprocals
+  int32_t rq_fast, score_clamp, pv_clamp;
+  uint32_t inv_I0;
+  float inv_ww;
 };
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s);
 hipError_t launch_qkv_relayout(const int8_t* qkv, int32_t B, const QkvLayout& L,

@@ -461,6 +461,33 @@ def test_attention_split_pv(case):
     assert np.mean(ref == 0) < 0.1 and np.mean(np.abs(ref) == 127) < 0.5
 
 
+@pytest.mark.parametrize("T,windows,I0", [
+    # few workgroups: 16-row blocks over 4 waves up to 512 keys, then 32-row
+    # blocks over 16 waves; the wave's slots 1, 2, 6, 8; 3, 4, 7, 8
+    (17, 3, 12), (65, 2, 12), (383, 1, 9), (512, 1, 16), (513, 3, 10), (800, 2, 12),
+    (1700, 1, 9), (2040, 1, 9),
+    # many: 32-row blocks over 4 waves (1, 3, 8 slots), over 8 waves (5, 9 all
+    # held as exponentials; 11, 13, 15 with some held as bytes)
+    (16, 512, 12), (150, 110, 12), (497, 33, 9), (520, 16, 12), (1100, 8, 9), (1401, 6, 9),
+    (1600, 6, 9), (1890, 5, 9),
+    # the general kernel (64-bit sums, or P with a clamp) at slots of both kinds
+    (1600, 6, 3000), (400, 40, 16383), (70, 3, 1),
+])
+@pytest.mark.parametrize("s_d", [-1, 3])
+def test_attention_slots(T, windows, I0, s_d):
+    """Every way the keys are dealt to waves and registers, with a partial
+    last block where T % 16 != 0 and waves that have no last slot."""
+    say(f"attention slots T={T} windows={windows} I0={I0} s_d={s_d}")
+    g = rng(T + windows + I0)
+    qkv = np.clip(np.round(g.normal(0, 42, (1, windows * T, 192))), -127, 127).astype(np.int8)
+    p = {"score_mult": (3 << 28) + 99, "score_shift": 38, "smax_I0": I0, "smax_s_d": s_d,
+         "pv_mult": (3 << 28) + 7, "pv_shift": 34}
+    ref = oracle.attention(qkv[0], windows, T, 1, T, 1, 64, p["score_mult"], p["score_shift"], I0,
+                           p["pv_mult"], p["pv_shift"], s_d=s_d)[None]
+    got = host(ilw.ilw_attention(dev(qkv), windows, T, 1, T, 1, p))
+    assert_same(got, ref, "attention slots")
+
+
 # (score_mult, score_shift): the unclamped score form covers shifts 32..54,
 # and smaller shifts when |acc * m / 2^s| stays inside int32 (|acc| <= 2^20);
 # the rest clamp the accumulator first.
