@@ -217,6 +217,28 @@ def test_shiftmax_row_chunks(rows, cols, s_d):
 
 
 # ------------------------------------------------------------------ SD-ShiftGELU
+@pytest.mark.parametrize("cols", [15, 16, 17, 49, 64, 65, 129, 193, 257, 300, 385, 513, 769, 1025,
+                                  1537, 2047, 2048, 2049])
+@pytest.mark.parametrize("offset", [0, 3])
+def test_shiftmax_ragged_rows(cols, offset):
+    """Rows that are no multiple of 16 long, at every split of a row over
+    lanes, from a base that is not aligned; in place too (the last two chunks
+    of a row overlap)."""
+    say(f"shiftmax ragged cols={cols} offset={offset}")
+    g = rng(cols + offset)
+    rows = 77
+    x = g.integers(-128, 128, (rows, cols)).astype(np.int8)
+    x[3] = 5  # a constant row
+    ref = oracle.shiftmax_rows(x, 12, s_d=-1)
+    buf = torch.zeros(rows * cols + 64, dtype=torch.int8, device="cuda")
+    xd = buf[offset:offset + rows * cols].view(rows, cols)
+    xd.copy_(torch.from_numpy(x))
+    assert_same(host(ilw.ilw_shiftmax(xd, 12)), ref, "shiftmax ragged")
+    ilw.ilw_shiftmax(xd, 12, y=xd)
+    assert_same(host(xd), ref, "shiftmax ragged in place")
+    assert int(buf[:offset].abs().sum()) == 0 and int(buf[offset + rows * cols:].abs().sum()) == 0
+
+
 @pytest.mark.parametrize("I0", [1, 8, 16, 37, 64, 1000, 16383])
 def test_sdshiftgelu_exhaustive(I0):
     say(f"sdshiftgelu exhaustive I0={I0}")
