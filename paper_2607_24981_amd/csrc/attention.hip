@@ -472,7 +472,7 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
 // [B, T, 3D] token-major QKV -> window-major Q, K and V (see QkvLayout).
 // One thread per 16-byte chunk of Q and K; the values go in groups of 4
 // consecutive keys: a thread loads a 16-channel chunk of each and stores 4
-// keys of a channel per word (byte stores of single keys made this 16.7 us
+// keys of 4 channels per 16 bytes (byte stores of single keys made this 16.7 us
 // against 7.0 at 4 x 1600 tokens of 384 channels).  n_qk and n_v are the two
 // parts' thread counts.
 __global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, QkvLayout L,
@@ -514,15 +514,10 @@ __global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, Qk
   int8_t* dst = L.vt + ((int64_t)bw * L.H + h) * 64 * L.Twp + vt_key(k0) + vt_channel(c);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    // 4 keys x 4 channels transposed
-    const uint32_t p01 = __builtin_amdgcn_perm((uint32_t)x[1][q], (uint32_t)x[0][q], 0x05010400u);
-    const uint32_t p23 = __builtin_amdgcn_perm((uint32_t)x[3][q], (uint32_t)x[2][q], 0x05010400u);
-    const uint32_t q01 = __builtin_amdgcn_perm((uint32_t)x[1][q], (uint32_t)x[0][q], 0x07030602u);
-    const uint32_t q23 = __builtin_amdgcn_perm((uint32_t)x[3][q], (uint32_t)x[2][q], 0x07030602u);
-    *(uint32_t*)(dst + vt_channel(4 * q + 0)) = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
-    *(uint32_t*)(dst + vt_channel(4 * q + 1)) = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
-    *(uint32_t*)(dst + vt_channel(4 * q + 2)) = __builtin_amdgcn_perm(q23, q01, 0x05040100u);
-    *(uint32_t*)(dst + vt_channel(4 * q + 3)) = __builtin_amdgcn_perm(q23, q01, 0x07060302u);
+    // 4 keys x 4 channels transposed: 16 consecutive bytes
+    const uint32_t w[4] = {(uint32_t)x[0][q], (uint32_t)x[1][q], (uint32_t)x[2][q],
+                           (uint32_t)x[3][q]};
+    *(v4i*)(dst + vt_channel(4 * q)) = transpose4(w);
   }
 }
 

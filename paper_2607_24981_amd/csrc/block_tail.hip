@@ -160,9 +160,10 @@ __device__ __forceinline__ void slab_qkv(const TailArgs& a, const v4i (&wq)[3][D
       int8_t* base = part == 0 ? Lq.q : Lq.k;
       *(uint32_t*)(base + tq + (int64_t)h * Lq.Tw * 64 + c) = pack4(v[0], v[1], v[2], v[3]);
     } else {
-      int8_t* dst = Lq.vt + tv + (int64_t)h * 64 * Lq.Twp + vt_channel(c);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) dst[vt_channel(r)] = (int8_t)v[r];
+      // (single bytes: the exchanges of whole quads would lengthen the chain at
+      // the end of a latency-bound kernel, 148.4 -> 149.4 us at batch 1)
+      vt_store(Lq.vt + tv + (int64_t)h * 64 * Lq.Twp + vt_channel(c), pack4(v[0], v[1], v[2], v[3]),
+               tl, false);
     }
   }
 }

@@ -352,6 +352,27 @@ struct RqI64 {
   }
 };
 
+// 4 x 4 bytes transposed among the 4 lanes of a quad: lane t's byte k becomes
+// lane k's byte t (two exchanges with a neighbour, two permutes).
+__device__ __forceinline__ uint32_t quad_transpose(uint32_t w, int lane) {
+  const uint32_t y = (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xb1, 0xf, 0xf, true);  // lane ^ 1
+  const uint32_t q = __builtin_amdgcn_perm(y, w, lane & 1 ? 0x03070105u : 0x06020400u);
+  const uint32_t z = (uint32_t)__builtin_amdgcn_mov_dpp((int)q, 0x4e, 0xf, 0xf, true);  // lane ^ 2
+  return __builtin_amdgcn_perm(z, q, lane & 2 ? 0x03020706u : 0x05040100u);
+}
+
+// The same of four words in one lane: output word c holds byte c of each.
+__device__ __forceinline__ v4i transpose4(const uint32_t (&w)[4]) {
+  const uint32_t a01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);  // bytes 0 0 1 1
+  const uint32_t a23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const uint32_t b01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);  // bytes 2 2 3 3
+  const uint32_t b23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+  return v4i{(int)__builtin_amdgcn_perm(a23, a01, 0x05040100u),
+             (int)__builtin_amdgcn_perm(a23, a01, 0x07060302u),
+             (int)__builtin_amdgcn_perm(b23, b01, 0x05040100u),
+             (int)__builtin_amdgcn_perm(b23, b01, 0x07060302u)};
+}
+
 template <bool B>
 struct Flag {
   static constexpr bool value = B;
@@ -396,6 +417,25 @@ __device__ __forceinline__ int32_t vt_key(int32_t k) {
   return (k >> 4) * 1024 + ((k >> 2) & 3) * 64 + (k & 3);
 }
 __device__ __forceinline__ int32_t vt_channel(int32_t c) { return (c >> 4) * 256 + (c & 15) * 4; }
+// True where 4 consecutive tokens from a multiple of 4 on are 4 consecutive
+// keys from a multiple of 4 on: their values then leave in one word per channel.
+__device__ __forceinline__ bool vt_quads(const QkvLayout& L) {
+  return ((L.win_w | L.grid_w) & 3) == 0;
+}
+// Stores the values of channels c .. c + 3 (one word, c a multiple of 4) of a
+// token: v is the V address of key 0's (window, head) plus vt_key of the
+// token's key plus vt_channel(c).  With quads (vt_quads; the tokens of the
+// lane's quad consecutive from a multiple of 4 on, and all valid) a lane
+// stores 4 keys of channel c + lane % 4, 256 consecutive bytes per wave;
+// otherwise the word's bytes one by one.
+__device__ __forceinline__ void vt_store(int8_t* v, uint32_t word, int lane, bool quads) {
+  if (quads) {
+    *(uint32_t*)(v - (lane & 3) + vt_channel(lane & 3)) = quad_transpose(word, lane);
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[vt_channel(r)] = (int8_t)(word >> (8 * r));
+  }
+}
 
 struct GemmArgs {
   const int8_t* x;   // [M, K] activations

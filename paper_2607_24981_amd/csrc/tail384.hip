@@ -44,6 +44,13 @@ __device__ __forceinline__ int blk_off(int kb, int row, int chunk) {
   return kb * T_BLK + lds_chunk<T_KB / 16>(row, chunk);
 }
 
+// Requantization with the accumulator clamp, or without it where every channel
+// of the launch's constants allows that (RqI64::init_bounded).
+template <bool CLAMP>
+__device__ __forceinline__ int32_t requant(const RqI64& q, int32_t acc) {
+  return CLAMP ? q.apply(acc) : q.apply_unclamped(acc);
+}
+
 // LayerNorm of one 384-wide result, 4 channels per word: row sums (byte dot
 // products, the 4 lanes of a token, the waves through LDS), then wave 0
 // turns them into each token's mean and 1 / sigma factor (one serial Newton
@@ -51,12 +58,13 @@ __device__ __forceinline__ int blk_off(int kb, int row, int chunk) {
 // its words.  lnred: [T_NW][T_TM][2], lnst: [T_TM][2].  `before` runs once
 // the sums are written and must end in a barrier; `during` runs on every
 // wave while wave 0 computes the statistics (after them on wave 0).
+// clamp (uniform): some channel needs the accumulator clamp.
 template <typename Before, typename During>
 __device__ __forceinline__ void layernorm_words(const uint32_t (&xw)[T_FI][T_FJ],
                                                 uint32_t (&yw)[T_FI][T_FJ], const RqI64* lnq,
                                                 int32_t iters, int32_t* lnred, int32_t* lnst,
                                                 const int32_t (&cw)[T_FI], int wave, int lane,
-                                                Before before, During during) {
+                                                bool clamp, Before before, During during) {
 #pragma unroll
   for (int j = 0; j < T_FJ; ++j) {
     int32_t S = 0, SS = 0;
@@ -90,21 +98,27 @@ __device__ __forceinline__ void layernorm_words(const uint32_t (&xw)[T_FI][T_FJ]
   }
   during();
   lds_sync();
+  auto outputs = [&](auto cl) {
 #pragma unroll
-  for (int j = 0; j < T_FJ; ++j) {
-    const int32_t mu = lnst[(j * 16 + (lane & 15)) * 2 + 0];
-    const int32_t F = lnst[(j * 16 + (lane & 15)) * 2 + 1];
+    for (int j = 0; j < T_FJ; ++j) {
+      const int32_t mu = lnst[(j * 16 + (lane & 15)) * 2 + 0];
+      const int32_t F = lnst[(j * 16 + (lane & 15)) * 2 + 1];
 #pragma unroll
-    for (int i = 0; i < T_FI; ++i) {
-      int32_t o[4];
+      for (int i = 0; i < T_FI; ++i) {
+        int32_t o[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int32_t d = (int8_t)(xw[i][j] >> (8 * r)) - mu;
-        o[r] = lnq[cw[i] + r].apply((d * F) >> 1);  // |d| <= sigma: |d * F| < 2^31
+        for (int r = 0; r < 4; ++r) {
+          const int32_t d = (int8_t)(xw[i][j] >> (8 * r)) - mu;
+          o[r] = requant<cl.value>(lnq[cw[i] + r], (d * F) >> 1);  // |d| <= sigma: |d F| < 2^31
+        }
+        yw[i][j] = pack4(o[0], o[1], o[2], o[3]);
       }
-      yw[i][j] = pack4(o[0], o[1], o[2], o[3]);
     }
-  }
+  };
+  if (clamp)
+    outputs(Flag<true>{});
+  else
+    outputs(Flag<false>{});
 }
 
 // fp: projection + residual (x = att, wp, resid = the block input, LN2's
@@ -123,7 +137,9 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   // SD-ShiftGELU of an int8 value, requantized.  Aligned so that it sits at
   // LDS address 0: a lookup's +128 then folds into the instruction offset.
   __shared__ __attribute__((aligned(1024))) int8_t glut[256];
-  __shared__ int32_t fc1_needs_clamp[T_NW];  // per wave: see the fc1 constants below
+  // per wave: a channel of the projection, LN2 or fc1 (0), of fc2 or the next
+  // LayerNorm (1), needs the accumulator clamp
+  __shared__ int32_t needs_clamp[2][T_NW];
   static_assert(2 * T_D * sizeof(RqI64) <= sizeof(sX), "fc2 constants fit the h tile");
   constexpr int RED = (T_NW + 1) * T_TM * 2 * 4;  // row sums and statistics
   static_assert(3 * T_BLK + 2 * T_D * sizeof(RqI64) + RED <= sizeof(sH), "projection phase fits");
@@ -195,45 +211,46 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
 #pragma unroll
   for (int i = 0; i < T_FI; ++i) cw[i] = wave * (16 * T_FI) + i * 16 + (lane >> 4) * 4;
   // constants, while the loads are in flight
+  bool cl = false;
   for (int c = tid; c < T_D; c += 64 * T_NW) {
     RqI64 r;
-    r.init_bounded(fp.mult[fp.nq == 1 ? 0 : c], fp.shift[fp.nq == 1 ? 0 : c],
-                   fp.bias ? fp.bias[c] : 0, kAccD);
+    cl |= !r.init_bounded(fp.mult[fp.nq == 1 ? 0 : c], fp.shift[fp.nq == 1 ? 0 : c],
+                          fp.bias ? fp.bias[c] : 0, kAccD);
     rqp[c] = r;
     const int qn = fp.ln_nq == 1 ? 0 : c;
-    r.init_bounded(fp.ln_mult[qn], fp.ln_shift[qn], fp.ln_beta[c], kAccLN);
+    cl |= !r.init_bounded(fp.ln_mult[qn], fp.ln_shift[qn], fp.ln_beta[c], kAccLN);
     lnq2[c] = r;
   }
-  // fc1's requantization skips the accumulator clamp when every channel
-  // allows it (RqI64::init_bounded)
-  bool needs_clamp = false;
   for (int c = tid; c < mlp; c += 64 * T_NW) {
     RqI64 r;
-    needs_clamp |= !r.init_bounded(f1.mult[f1.nq == 1 ? 0 : c], f1.shift[f1.nq == 1 ? 0 : c],
-                                   f1.bias ? f1.bias[c] : 0, kAccD);
+    cl |= !r.init_bounded(f1.mult[f1.nq == 1 ? 0 : c], f1.shift[f1.nq == 1 ? 0 : c],
+                          f1.bias ? f1.bias[c] : 0, kAccD);
     rq1[c] = r;
   }
-  const bool wave_needs = __any(needs_clamp);
-  if (lane == 0) fc1_needs_clamp[wave] = wave_needs;
   if (tid < 256)
     glut[tid] = (int8_t)rq(sd_gelu(tid - 128, f1.g_I0, f1.g_kinter, f1.g_kout), f1.g_mult,
                            f1.g_shift);
-  lds_sync();
-  int32_t any_needs = 0;
+  auto say_clamp = [&](int k, bool v) {
+    const bool any = __any(v);
+    if (lane == 0) needs_clamp[k][wave] = any;
+  };
+  auto any_clamp = [&](int k) {
+    int32_t any = 0;
 #pragma unroll
-  for (int w = 0; w < T_NW; ++w) any_needs |= fc1_needs_clamp[w];
-  const bool fc1_unclamped = __builtin_amdgcn_readfirstlane(any_needs) == 0;
+    for (int v = 0; v < T_NW; ++v) any |= needs_clamp[k][v];
+    return __builtin_amdgcn_readfirstlane(any) != 0;
+  };
+  say_clamp(0, cl);
+  lds_sync();
+  const bool clamp1 = any_clamp(0);
 
   v4i acc[T_FI][T_FJ];
   const v4i zero = {0, 0, 0, 0};
-#pragma unroll
-  for (int i = 0; i < T_FI; ++i)
-#pragma unroll
-    for (int j = 0; j < T_FJ; ++j) acc[i][j] = zero;
   // fragment rows start at multiples of 16: the swizzle depends on lane % 16
   const int fo[2] = {lds_chunk<T_KB / 16>(lane & 15, lane >> 4),
                      lds_chunk<T_KB / 16>(lane & 15, 4 + (lane >> 4))};
-  auto compute = [&](const int8_t* blk, const v4i(&wf)[2][T_FI]) {
+  // (fresh: the products start new sums)
+  auto compute = [&](const int8_t* blk, const v4i(&wf)[2][T_FI], bool fresh) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       v4i fb[T_FJ];
@@ -243,18 +260,22 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
       for (int i = 0; i < T_FI; ++i)
 #pragma unroll
         for (int j = 0; j < T_FJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf[h][i], fb[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              wf[h][i], fb[j], fresh && h == 0 ? zero : acc[i][j], 0, 0, 0);
     }
   };
   // one ring turn: steps k0 .. k0 + 2 from the 3 blocks at base (stride
   // T_BLK); step k loads step k + 2 (clamped to the last step: a re-read,
   // never used)
-  auto turn = [&](int k0, const int8_t* base) {
+  auto turn = [&](int k0, const int8_t* base, auto fresh) {
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
       wload(w[(u + 2) % 3], min(k0 + u + 2, S - 1));
-      compute(base + u * T_BLK, w[u]);
+      compute(base + u * T_BLK, w[u], decltype(fresh)::value && u == 0);
     }
+    // (what follows a turn loads nothing before its end)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
   };
   // a word of 4 channels of token t into block layout tile (channel n, a
   // multiple of 4)
@@ -267,16 +288,16 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   // x1 = Res(rq(acc), x) stays in xw1, h = LN2(x1) goes to sX.  After each
   // fc1 chunk: requantize, SD-ShiftGELU by table, into sH.
   uint32_t xw1[T_FI][T_FJ];
-  for (int k0 = 0; k0 < S; k0 += 3) {
-    turn(k0, k0 < S0 ? sH : (k0 < S1 ? sX : sH + (k0 - S1) * T_BLK));
-    if (k0 < S0) {
-      uint32_t rs[T_FI][T_FJ];  // the block input x: the projection's residual
+  turn(0, sH, Flag<true>{});
+  {
+    uint32_t rs[T_FI][T_FJ];  // the block input x: the projection's residual
 #pragma unroll
-      for (int j = 0; j < T_FJ; ++j) {
-        const int64_t m = min(m0 + j * 16 + (lane & 15), M - 1);
+    for (int j = 0; j < T_FJ; ++j) {
+      const int64_t m = min(m0 + j * 16 + (lane & 15), M - 1);
 #pragma unroll
-        for (int i = 0; i < T_FI; ++i) rs[i][j] = *(const uint32_t*)(fp.resid + m * T_D + cw[i]);
-      }
+      for (int i = 0; i < T_FI; ++i) rs[i][j] = *(const uint32_t*)(fp.resid + m * T_D + cw[i]);
+    }
+    auto project = [&](auto c) {
 #pragma unroll
       for (int i = 0; i < T_FI; ++i) {
         RqI64 rf[4];
@@ -287,85 +308,92 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
           int32_t o[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            o[r] = rq2i8<WIDE1>(rf[r].apply(acc[i][j][r]), (int8_t)(rs[i][j] >> (8 * r)),
-                                fp.res_ma, fp.res_mb, fp.res_shift);
+            o[r] = rq2i8<WIDE1>(requant<c.value>(rf[r], acc[i][j][r]),
+                                (int8_t)(rs[i][j] >> (8 * r)), fp.res_ma, fp.res_mb, fp.res_shift);
           xw1[i][j] = pack4(o[0], o[1], o[2], o[3]);
-          acc[i][j] = zero;
         }
       }
-      uint32_t hw[T_FI][T_FJ];
-      layernorm_words(xw1, hw, lnq2, fp.ln_iters, red1, red1 + T_NW * T_TM * 2, cw, wave, lane,
-                      [] { lds_sync(); }, [] {});
+    };
+    if (clamp1)
+      project(Flag<true>{});
+    else
+      project(Flag<false>{});
+    uint32_t hw[T_FI][T_FJ];
+    layernorm_words(xw1, hw, lnq2, fp.ln_iters, red1, red1 + T_NW * T_TM * 2, cw, wave, lane,
+                    clamp1, [] { lds_sync(); }, [] {});
 #pragma unroll
-      for (int i = 0; i < T_FI; ++i)
+    for (int i = 0; i < T_FI; ++i)
 #pragma unroll
-        for (int j = 0; j < T_FJ; ++j) put_word(sX, cw[i], j * 16 + (lane & 15), hw[i][j]);
-      lds_sync();  // h complete; the attention tile and its constants no longer read
-    } else if (k0 < S1) {
-      const int q = (k0 - S0) / 3;
+      for (int j = 0; j < T_FJ; ++j) put_word(sX, cw[i], j * 16 + (lane & 15), hw[i][j]);
+    lds_sync();  // h complete; the attention tile and its constants no longer read
+  }
+  for (int q = 0; q < nch; ++q) {
+    turn(S0 + 3 * q, sX, Flag<true>{});
+    auto activate = [&](auto c) {
 #pragma unroll
       for (int i = 0; i < T_FI; ++i) {
         const int32_t n = q * T_D + cw[i];
         RqI64 rf[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) rf[r] = rq1[n + r];
-        if (fc1_unclamped) {
 #pragma unroll
-          for (int j = 0; j < T_FJ; ++j) {
-            int32_t g[4];
+        for (int j = 0; j < T_FJ; ++j) {
+          int32_t g[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) g[r] = glut[rf[r].apply_unclamped(acc[i][j][r]) + 128];
-            put_word(sH, n, j * 16 + (lane & 15), pack4(g[0], g[1], g[2], g[3]));
-            acc[i][j] = zero;
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < T_FJ; ++j) {
-            int32_t g[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) g[r] = glut[rf[r].apply(acc[i][j][r]) + 128];
-            put_word(sH, n, j * 16 + (lane & 15), pack4(g[0], g[1], g[2], g[3]));
-            acc[i][j] = zero;
-          }
+          for (int r = 0; r < 4; ++r) g[r] = glut[requant<c.value>(rf[r], acc[i][j][r]) + 128];
+          put_word(sH, n, j * 16 + (lane & 15), pack4(g[0], g[1], g[2], g[3]));
         }
       }
-      if (k0 + 3 == S1) {
-        // fc1 done: its outputs complete, the h tile free for the fc2 and
-        // LayerNorm constants (first used after the closing barrier)
-        lds_sync();
-        for (int c = tid; c < T_D; c += 64 * T_NW) {
-          RqI64 r;
-          r.init_bounded(f2.mult[f2.nq == 1 ? 0 : c], f2.shift[f2.nq == 1 ? 0 : c],
-                         f2.bias ? f2.bias[c] : 0, (uint32_t)mlp << 14);
-          rq2[c] = r;
-          if (DO_LN) {
-            const int qn = f2.ln_nq == 1 ? 0 : c;
-            r.init_bounded(f2.ln_mult[qn], f2.ln_shift[qn], f2.ln_beta[c], kAccLN);
-            lnq[c] = r;
-          }
-        }
-      }
+    };
+    if (clamp1)
+      activate(Flag<true>{});
+    else
+      activate(Flag<false>{});
+  }
+  // fc1 done: its outputs complete, the h tile free for the fc2 and
+  // LayerNorm constants (first used after the closing barrier)
+  lds_sync();
+  cl = false;
+  for (int c = tid; c < T_D; c += 64 * T_NW) {
+    RqI64 r;
+    cl |= !r.init_bounded(f2.mult[f2.nq == 1 ? 0 : c], f2.shift[f2.nq == 1 ? 0 : c],
+                          f2.bias ? f2.bias[c] : 0, (uint32_t)mlp << 14);
+    rq2[c] = r;
+    if (DO_LN) {
+      const int qn = f2.ln_nq == 1 ? 0 : c;
+      cl |= !r.init_bounded(f2.ln_mult[qn], f2.ln_shift[qn], f2.ln_beta[c], kAccLN);
+      lnq[c] = r;
     }
   }
+  say_clamp(1, cl);
+  turn(S1, sH, Flag<true>{});
+  for (int k0 = S1 + 3; k0 < S; k0 += 3) turn(k0, sH + (k0 - S1) * T_BLK, Flag<false>{});
 
   // ---- fc2's result: residual onto x1, the next LayerNorm
   lds_sync();  // fc2's reads of sH done; its constants visible
+  const bool clamp2 = any_clamp(1);
   uint32_t xw[T_FI][T_FJ];
+  auto finish = [&](auto c) {
 #pragma unroll
-  for (int i = 0; i < T_FI; ++i) {
-    RqI64 rf[4];
+    for (int i = 0; i < T_FI; ++i) {
+      RqI64 rf[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) rf[r] = rq2[cw[i] + r];
+      for (int r = 0; r < 4; ++r) rf[r] = rq2[cw[i] + r];
 #pragma unroll
-    for (int j = 0; j < T_FJ; ++j) {
-      int32_t o[4];
+      for (int j = 0; j < T_FJ; ++j) {
+        int32_t o[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        o[r] = rq2i8<WIDE2>(rf[r].apply(acc[i][j][r]), (int8_t)(xw1[i][j] >> (8 * r)), f2.res_ma,
-                            f2.res_mb, f2.res_shift);
-      xw[i][j] = pack4(o[0], o[1], o[2], o[3]);
+        for (int r = 0; r < 4; ++r)
+          o[r] = rq2i8<WIDE2>(requant<c.value>(rf[r], acc[i][j][r]),
+                              (int8_t)(xw1[i][j] >> (8 * r)), f2.res_ma, f2.res_mb, f2.res_shift);
+        xw[i][j] = pack4(o[0], o[1], o[2], o[3]);
+      }
     }
-  }
+  };
+  if (clamp2)
+    finish(Flag<true>{});
+  else
+    finish(Flag<false>{});
   // Both outputs leave through LDS token rows as 16-byte row chunks; wave 0
   // turns the row sums into the tokens' statistics while the others copy the
   // block output out.
@@ -405,6 +433,7 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   // (the barrier after `during` also ends every read of the staged y)
   layernorm_words(
       xw, yw, lnq, f2.ln_iters, red2, red2 + T_NW * T_TM * 2, cw, wave, lane,
+      clamp2,
       [&] {
         stage(xw);
         lds_sync();

@@ -695,6 +695,28 @@ def test_block_large_unpacked(dims, B, win):
         assert_same(got[b:b + 1], ref, f"block large image {b}")
 
 
+@pytest.mark.parametrize("dims,grid,win,B", [
+    ((192, 3, 768), (21, 22), (7, 11), 24),    # keys leave one by one
+    ((192, 3, 768), (21, 24), (7, 12), 23),    # 4 keys x 4 channels at a time
+    ((384, 6, 1536), (18, 19), (9, 19), 12),   # the 256-channel tile, one by one
+    ((384, 6, 1536), (19, 20), (19, 4), 12),   # 4 x 4
+    ((128, 2, 512), (5, 4), (5, 4), 500),      # 384 channels, Q | K | V inside one tile
+])
+def test_block_qkv_scatter(dims, grid, win, B):
+    """The QKV epilogue's window-major stores on grids past the latency tiles:
+    windows whose keys do and do not fall in groups of 4."""
+    D, H, Hm = dims
+    gh, gw = grid
+    say(f"block QKV scatter D={D} grid={gh}x{gw} win={win} B={B}")
+    p = synth.block_params(rng(61 + D + gw), D, H, 64, Hm, "wide")
+    p["smax_I0"] = 10
+    x = np.clip(np.round(rng(62).normal(0, 42, (B, gh * gw, D))), -127, 127).astype(np.int8)
+    got = host(ilw.ilw_block_forward(ilw.DeviceBlock(p), dev(x), gh, gw, *win))
+    for i in sorted({0, B // 2, B - 1}):
+        ref = oracle.block_forward(p, x[i:i + 1], gh, gw, *win)
+        assert_same(got[i:i + 1], ref, f"image {i}")
+
+
 @pytest.mark.parametrize("dims", [(128, 2, 512), (384, 6, 1536)])
 def test_block_requant_fallback(dims):
     """A block whose QKV, projection, fc1 and fc2 layers each hold a channel
