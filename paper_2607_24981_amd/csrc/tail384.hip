@@ -9,12 +9,13 @@
 //   y  = Res(rq(g W2^T + b2), x1)               -> y   (the block's output)
 //   h' = LN1 of the next block (y)              -> y2  (optional)
 //
-// A workgroup holds 64 tokens.  Each of its 12 waves owns 32 channels of all
-// 64 tokens in every 384-wide result (projection, each 384-channel chunk of
-// fc1, fc2) and loads its weight fragments from global memory straight into
-// MFMA A-operand registers, two K steps ahead in a ring of three register
-// sets: the projection's 3 K steps, fc1's 3 per chunk and fc2's mlp / 128
-// form one stream.  The activation operands are LDS tiles of 64 rows with
+// A workgroup holds 64 tokens (16 or 32 where the launch has few: see
+// launch_tail384).  Each of its 12 waves owns 32 channels of all its tokens
+// in every 384-wide result (projection, each 384-channel chunk of fc1, fc2)
+// and loads its weight fragments from global memory straight into MFMA
+// A-operand registers, two K steps ahead in a ring of three register sets:
+// the projection's 3 K steps, fc1's 3 per chunk and fc2's mlp / 128 form one
+// stream.  The activation operands are LDS tiles of 16-token row groups with
 // swizzled 128-byte blocks: the attention output, then h (written by the
 // projection's LayerNorm epilogue), then the fc1 output (written chunk by
 // chunk, SD-ShiftGELU by table).  In the accumulator layout a lane holds 4
@@ -27,22 +28,24 @@
 namespace ilw {
 namespace {
 
-constexpr int T_D = 384, T_TM = 64, T_FJ = 4, T_NW = 12, T_FI = 2;
+constexpr int T_D = 384, T_NW = 12, T_FI = 2;
 constexpr int T_KB = 128;                    // K bytes per step
-constexpr int T_BLK = T_TM * T_KB;           // one 64 x 128 activation block in LDS
 constexpr int T_MAXCH = 4;                   // fc1 chunks of 384 channels at most
 constexpr int T_OSTR = T_D / 4 + 4;          // output staging: words per token row
-constexpr int NXCD_T = 8;
+constexpr int NXCD_T = 8, NCU = 256;
 // accumulator bounds for the requantization constants: a 384-deep int8
 // product; a LayerNorm's (d F) >> 1, with |d| <= sigma and F < 2^31 / sigma
 constexpr uint32_t kAccD = (uint32_t)T_D << 14, kAccLN = 1u << 30;
 static_assert(T_FI * T_NW * 16 == T_D, "whole fragments per wave");
 
-// block kb of an activation tile: rows of 128 bytes with swizzled chunks
-// (lds_chunk), blocks of 8 KB
+// block kb of an activation tile of TM rows: rows of 128 bytes with swizzled
+// chunks (lds_chunk)
+template <int TM>
 __device__ __forceinline__ int blk_off(int kb, int row, int chunk) {
-  return kb * T_BLK + lds_chunk<T_KB / 16>(row, chunk);
+  return kb * TM * T_KB + lds_chunk<T_KB / 16>(row, chunk);
 }
+
+constexpr int larger(int a, int b) { return a > b ? a : b; }
 
 // Requantization with the accumulator clamp, or without it where every channel
 // of the launch's constants allows that (RqI64::init_bounded).
@@ -59,12 +62,13 @@ __device__ __forceinline__ int32_t requant(const RqI64& q, int32_t acc) {
 // the sums are written and must end in a barrier; `during` runs on every
 // wave while wave 0 computes the statistics (after them on wave 0).
 // clamp (uniform): some channel needs the accumulator clamp.
-template <typename Before, typename During>
+template <int T_FJ, typename Before, typename During>
 __device__ __forceinline__ void layernorm_words(const uint32_t (&xw)[T_FI][T_FJ],
                                                 uint32_t (&yw)[T_FI][T_FJ], const RqI64* lnq,
                                                 int32_t iters, int32_t* lnred, int32_t* lnst,
                                                 const int32_t (&cw)[T_FI], int wave, int lane,
                                                 bool clamp, Before before, During during) {
+  constexpr int T_TM = 16 * T_FJ;
 #pragma unroll
   for (int j = 0; j < T_FJ; ++j) {
     int32_t S = 0, SS = 0;
@@ -83,7 +87,7 @@ __device__ __forceinline__ void layernorm_words(const uint32_t (&xw)[T_FI][T_FJ]
     }
   }
   before();  // ends with a barrier
-  if (wave == 0) {
+  if (wave == 0 && lane < T_TM) {
     int32_t s = 0, ss = 0;
 #pragma unroll
     for (int w = 0; w < T_NW; ++w) {
@@ -124,15 +128,21 @@ __device__ __forceinline__ void layernorm_words(const uint32_t (&xw)[T_FI][T_FJ]
 // fp: projection + residual (x = att, wp, resid = the block input, LN2's
 // fields); f1: fc1 + SD-ShiftGELU (wp, N = mlp, the GELU fields); f2: fc2 +
 // residual (wp, y, with DO_LN the next LayerNorm's fields and y2).
-template <bool WIDE1, bool WIDE2, bool DO_LN>
+// T_FJ: groups of 16 tokens per workgroup.
+template <bool WIDE1, bool WIDE2, bool DO_LN, int T_FJ>
 __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArgs f1, GemmArgs f2,
                                                             int64_t tiles) {
+  constexpr int T_TM = 16 * T_FJ;
+  constexpr int T_BLK = T_TM * T_KB;  // one T_TM x 128 activation block in LDS
   // sX: h, the fc1 input (3 blocks); after fc1, the fc2 and LayerNorm output
   // constants.  sH: first the attention output (3 blocks), the projection's
   // and LN2's constants and their row sums; then the fc1 output (mlp / 128
   // blocks); after fc2's K loop the output staging rows and row sums.
-  __shared__ __attribute__((aligned(16))) int8_t sX[3 * T_BLK];
-  __shared__ __attribute__((aligned(16))) int8_t sH[3 * T_MAXCH * T_BLK];
+  constexpr int RED = (T_NW + 1) * T_TM * 2 * 4;  // row sums and statistics
+  constexpr int CONSTS = 2 * T_D * (int)sizeof(RqI64);
+  __shared__ __attribute__((aligned(16))) int8_t sX[larger(3 * T_BLK, CONSTS)];
+  __shared__ __attribute__((aligned(16))) int8_t
+      sH[larger(3 * T_MAXCH * T_BLK, larger(3 * T_BLK + CONSTS + RED, T_TM * T_OSTR * 4 + RED))];
   __shared__ RqI64 rq1[T_MAXCH * T_D];  // fc1 output requantization per channel
   // SD-ShiftGELU of an int8 value, requantized.  Aligned so that it sits at
   // LDS address 0: a lookup's +128 then folds into the instruction offset.
@@ -140,10 +150,6 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   // per wave: a channel of the projection, LN2 or fc1 (0), of fc2 or the next
   // LayerNorm (1), needs the accumulator clamp
   __shared__ int32_t needs_clamp[2][T_NW];
-  static_assert(2 * T_D * sizeof(RqI64) <= sizeof(sX), "fc2 constants fit the h tile");
-  constexpr int RED = (T_NW + 1) * T_TM * 2 * 4;  // row sums and statistics
-  static_assert(3 * T_BLK + 2 * T_D * sizeof(RqI64) + RED <= sizeof(sH), "projection phase fits");
-  static_assert(T_TM * T_OSTR * 4 + RED <= sizeof(sH), "staging rows and row sums fit");
   // projection phase
   RqI64* const rqp = (RqI64*)(sH + 3 * T_BLK);  // projection output requantization
   RqI64* const lnq2 = rqp + T_D;                // LN2 output requantization
@@ -196,13 +202,14 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   wload(w[0], 0);
   wload(w[1], 1);
 
-  // the attention output tile: 64 rows x 24 chunks, two chunks per thread
+  // the attention output tile: T_TM rows x 24 chunks
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int c = tid + u * 64 * T_NW;
+  for (int c0 = 0; c0 < T_TM * 24; c0 += 64 * T_NW) {
+    const int c = c0 + tid;
+    if ((T_TM * 24) % (64 * T_NW) != 0 && c >= T_TM * 24) break;
     const int r = c / 24, q = c - r * 24;
     const v4i v = *(const v4i*)(fp.x + min(m0 + r, M - 1) * T_D + q * 16);
-    *(v4i*)(sH + blk_off(q >> 3, r, q & 7)) = v;
+    *(v4i*)(sH + blk_off<T_TM>(q >> 3, r, q & 7)) = v;
   }
   // Lane: channels c_i .. c_i + 3 (c_i = 32 wave + 16 i + 4 (lane / 16)) of
   // token t_j = 16 j + lane % 16 of every 384-wide result.  Tokens past M
@@ -280,7 +287,7 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   // a word of 4 channels of token t into block layout tile (channel n, a
   // multiple of 4)
   auto put_word = [&](int8_t* tilebase, int n, int t, uint32_t word) {
-    *(uint32_t*)(tilebase + blk_off(n >> 7, t, (n & 127) >> 4) + (n & 15)) = word;
+    *(uint32_t*)(tilebase + blk_off<T_TM>(n >> 7, t, (n & 127) >> 4) + (n & 15)) = word;
   };
 
   // The stream, one ring turn (3 K steps) per iteration: the projection's
@@ -444,20 +451,31 @@ __global__ __launch_bounds__(64 * T_NW) void tail384_kernel(GemmArgs fp, GemmArg
   copy_out(f2.y2);
 }
 
-template <bool W1, bool W2>
+template <bool W1, bool W2, int FJ>
 void tail384_launch(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs& f2, bool layernorm,
-                    int64_t tiles, hipStream_t s) {
+                    hipStream_t s) {
+  const int64_t tiles = (fp.M + 16 * FJ - 1) / (16 * FJ);
   const dim3 grid((unsigned)tiles), block(64 * T_NW);
   if (layernorm)
-    hipLaunchKernelGGL((tail384_kernel<W1, W2, true>), grid, block, 0, s, fp, f1, f2, tiles);
+    hipLaunchKernelGGL((tail384_kernel<W1, W2, true, FJ>), grid, block, 0, s, fp, f1, f2, tiles);
   else
-    hipLaunchKernelGGL((tail384_kernel<W1, W2, false>), grid, block, 0, s, fp, f1, f2, tiles);
+    hipLaunchKernelGGL((tail384_kernel<W1, W2, false, FJ>), grid, block, 0, s, fp, f1, f2, tiles);
+}
+
+template <int FJ>
+void tail384_tile(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs& f2, bool layernorm,
+                  hipStream_t s) {
+  const bool w1 = fp.res_shift < 9, w2 = f2.res_shift < 9;
+  if (w1 && w2) tail384_launch<true, true, FJ>(fp, f1, f2, layernorm, s);
+  else if (w1) tail384_launch<true, false, FJ>(fp, f1, f2, layernorm, s);
+  else if (w2) tail384_launch<false, true, FJ>(fp, f1, f2, layernorm, s);
+  else tail384_launch<false, false, FJ>(fp, f1, f2, layernorm, s);
 }
 
 }  // namespace
 
-// Any token count: at batch 1 to 4 of the 1600-token 384-wide encoder (25 to
-// 100 workgroups) the kernel still beats the latency-mode GEMM tiles.
+// Any token count: at batch 1 to 4 of the 1600-token 384-wide encoder the
+// kernel beats the latency-mode GEMM tiles with 64 tokens a workgroup already.
 bool tail384_kernel_applies(int64_t M, int32_t D, int32_t mlp) {
   return M > 0 && D == T_D && mlp > 0 && mlp % T_D == 0 && mlp / T_D <= T_MAXCH;
 }
@@ -468,12 +486,19 @@ hipError_t launch_tail384(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs
   if (!tail384_kernel_applies(fp.M, fp.N, f1.N) || fp.K != T_D || f1.K != T_D ||
       f2.K != f1.N || f2.N != T_D || !fp.wp || !f1.wp || !f2.wp)
     return hipErrorInvalidValue;
-  const int64_t tiles = (fp.M + T_TM - 1) / T_TM;
-  const bool w1 = fp.res_shift < 9, w2 = f2.res_shift < 9;
-  if (w1 && w2) tail384_launch<true, true>(fp, f1, f2, layernorm, tiles, s);
-  else if (w1) tail384_launch<true, false>(fp, f1, f2, layernorm, tiles, s);
-  else if (w2) tail384_launch<false, true>(fp, f1, f2, layernorm, tiles, s);
-  else tail384_launch<false, false>(fp, f1, f2, layernorm, tiles, s);
+  // Tokens per workgroup: the fewest that keep the grid within one workgroup
+  // per CU.  Up to there a launch takes as long as one workgroup, whose time
+  // is its epilogues' VALU work (proportional to its tokens) above the weight
+  // stream (1.3 MB through one CU whatever its tokens: 8.6 us at 64 bytes a
+  // cycle); past it the smaller tiles only read the weights more often.
+  // Whole blocks (mlp 1536, us) with 16 / 32 / 64 tokens a workgroup:
+  //   256 tokens 36.7 / 39.7 / 44.6    2048 tokens 39.9 / 42.0 / 48.0
+  //   4096       43.4 / 45.0 / 51.4    7168        65.4 / 53.1 / 58.6
+  //   8192       67.2 / 54.9 / 59.4    12288       90.8 / 79.0 / 67.2
+  //   16384     116.5 / 89.9 / 79.0    32768      207.8 / 156.1 / 139.0
+  if (fp.M <= 16 * NCU) tail384_tile<1>(fp, f1, f2, layernorm, s);
+  else if (fp.M <= 32 * NCU) tail384_tile<2>(fp, f1, f2, layernorm, s);
+  else tail384_tile<4>(fp, f1, f2, layernorm, s);
   return hipGetLastError();
 }
 

@@ -847,6 +847,23 @@ def test_encoder_mid_batches(name, batch):
         assert_same(full[b:b + 1], refs[b], f"{wl.name} batch {batch} image {b}")
 
 
+@pytest.mark.parametrize("batch,hidden", [(1, 1536), (163, 1536), (164, 768), (327, 1536),
+                                          (328, 1536)])
+def test_block_tail_token_groups(batch, hidden):
+    """The 384-wide block tail on 16, 32 and 64 tokens a workgroup, at ragged
+    token counts on both sides of each change (4075, 4100, 8175, 8200 tokens)
+    and the smallest, with and without the next block's LayerNorm: the first,
+    a middle and the last image against the oracle."""
+    D, H, gh, gw = 384, 6, 5, 5
+    say(f"block tail token groups batch={batch} hidden={hidden}")
+    blocks = [synth.block_params(rng(90 + i), D, H, 64, hidden, "wide") for i in range(2)]
+    x = np.clip(np.round(rng(93).normal(0, 42, (batch, gh * gw, D))), -127, 127).astype(np.int8)
+    got = host(ilw.Encoder(blocks, [(gh, gw)] * 2, gh, gw).forward(dev(x)))
+    for i in sorted({0, batch // 2, batch - 1}):
+        assert_same(got[i:i + 1], encoder_ref(blocks, [(gh, gw)] * 2, x[i:i + 1], gh, gw),
+                    f"image {i}")
+
+
 def test_encoder_c4_full():
     """The tiny encoder at batch 32 (51 200 tokens per layer) with the
     specified parameter distributions: all 32 images against the oracle."""
@@ -899,8 +916,8 @@ def _encoder_case(D, H, Hm, depth, seed, variant="wide"):
     (128, 2, 512, (6, 8), [(3, 4), (0, 0)], 2),
     # one block: no next block to fuse LN1 into
     (192, 3, 384, (8, 8), [(4, 4)], 1),
-    # 384 channels, 15 tokens: the one-kernel block tail on a single,
-    # mostly empty 64-token tile; MLP 768 (two fc1 chunks)
+    # 384 channels, 15 tokens: the one-kernel block tail on a single ragged
+    # token tile; MLP 768 (two fc1 chunks)
     (384, 6, 768, (3, 5), [(0, 0), (3, 5)], 1),
 ])
 def test_encoder_shapes(D, H, Hm, grid, windows, B):
