@@ -26,13 +26,6 @@ __device__ __forceinline__ int32_t rq(int32_t acc, int32_t mult, int32_t shift) 
   return sat8(v >> shift);  // arithmetic shift: floor division by 2^shift
 }
 
-// Same for a 64-bit value, through an exact 128-bit product.
-__device__ __forceinline__ int32_t rq_wide(int64_t acc, int32_t mult, int32_t shift) {
-  __int128 v = (__int128)acc * mult + ((__int128)1 << (shift - 1));
-  v >>= shift;
-  return v > kQmax ? kQmax : (v < kQmin ? kQmin : (int32_t)v);
-}
-
 // Two-input dyadic add onto one scale (|a*ma| + |b*mb| < 2^39).
 __device__ __forceinline__ int32_t rq2(int32_t a, int32_t b, int32_t ma, int32_t mb,
                                        int32_t shift) {

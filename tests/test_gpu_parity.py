@@ -1474,6 +1474,24 @@ def test_deform_lane_groups(mode, boxes, dh, levels, P):
     assert_same(got, ref, "deform lane groups")
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("P,mult,sh", [(1, 1 << 30, 46), (2, (1 << 31) - 1, 1), (3, 1, 1),
+                                       (5, 1 << 30, 30), (7, 3, 5)])
+def test_deform_sample_chunks(mode, P, mult, sh):
+    """Sample counts around the chunks of gathers (3, 6, 9, 15 and 21 samples
+    on 8 lanes), the last query group of a workgroup idle, and the output
+    requantization at both ends of its multiplier and shift."""
+    say(f"deform sample chunks P={P} mult={mult} shift={sh} mode={mode}")
+    wl = synth.DeformWorkload("c", 2, 7, 96, 3, 32, ((9, 13), (4, 6), (2, 3)), P)
+    d = synth.deform_inputs(wl, 70 + P, boxes=True)
+    entry = ilw.ilw_deform_attn_boxes
+    ref = oracle.deform_attn(d["value"], d["level_hw"], d["level_start"], d["ref"],
+                             d["offsets"], d["logits"], d["I0"], mult, sh, mode)
+    got = host(entry(dev(d["value"]), d["level_hw"], d["level_start"], dev(d["ref"]),
+                     dev(d["offsets"]), dev(d["logits"]), d["I0"], mult, sh, mode))
+    assert_same(got, ref, "deform sample chunks")
+
+
 # (k_inter, k_out, m_p, s_d, I0) of the sampling weights' Constrained Shiftmax
 DEFORM_SMAX = [(16, 4, 4, -1, 16), (8, 2, 0, -1, 16), (12, 6, 31, -1, 16),
                (16, 8, 4, 20, 16383), (16, 8, 4, 31, 16383), (1, 3, 4, 0, 1),
