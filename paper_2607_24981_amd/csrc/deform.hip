@@ -167,13 +167,21 @@ __global__ __launch_bounds__(256) void deform_kernel(DeformArgs a) {
   *(uint32_t*)(a.out + grp * a.Dh + cl * 4) = packed;
 }
 
-// The same sampler without the per-lane redundancy, for G = head_dim / 4 a
-// power of two in [4, 64] (groups then align with waves): lane k of a group
+// Lanes per group for a head of `words` 4-channel words: the next power of
+// two, at least 4.
+__host__ __device__ __forceinline__ int32_t group_lanes(int32_t words) {
+  int32_t g = 4;
+  while (g < words) g <<= 1;
+  return g;
+}
+
+// The same sampler without the per-lane redundancy, on groups of
+// G = group_lanes(head_dim) lanes that align with waves: lane k of a group
 // owns samples k, k + G, ..., computes their Shiftmax weights and the value
 // words they read, the group combines the row maximum and the exponential sum
 // with XOR shuffles, and each sample's (words, weights) reach the G lanes of
 // its group through LDS.  J = ceil(L*P / G) samples per lane; MODE 0 nearest,
-// 1 bilinear.
+// 1 bilinear.  The first head_dim / 4 lanes of a group sum and store.
 //
 // A decoder's call has a few waves per SIMD, so a wave's own chain of
 // latencies and instructions is the time: everything the lanes read of their
@@ -196,7 +204,7 @@ __global__ __launch_bounds__(256) void deform_group_kernel(DeformArgs a) {
   __shared__ Weights sweights[256 * J + 64];
   __shared__ int32_t elut[256];
 
-  const int32_t G = a.Dh >> 2, gs = __builtin_ctz(G);
+  const int32_t words = a.Dh >> 2, G = group_lanes(words), gs = __builtin_ctz(G);
   const int32_t cl = threadIdx.x & (G - 1);
   const uint32_t ngrp = (uint32_t)a.B * a.Q * a.H;  // below 2^31: the host's rule
   const int64_t grp0 = ((int64_t)xcd_block() * 256 + threadIdx.x) >> gs;
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(256) void deform_group_kernel(DeformArgs a) {
   auto box_loc = [&](int64_t num) {
     return pshift >= 0 ? num >> pshift : floor_div_pos(num, den);
   };
-  const uint32_t row_words = (uint32_t)a.H * (uint32_t)G;
+  const uint32_t row_words = (uint32_t)a.H * (uint32_t)words;
 
   // the lane's own samples (off the map: word 0 with weight 0)
 #pragma unroll
@@ -297,7 +305,8 @@ __global__ __launch_bounds__(256) void deform_group_kernel(DeformArgs a) {
 
   // every sample of the group; slots past L*P hold weight 0
   const uint32_t* vbase = (const uint32_t*)a.value +
-                          (int64_t)(bq / (uint32_t)a.Q) * a.S * row_words + h * (uint32_t)G + cl;
+                          (int64_t)(bq / (uint32_t)a.Q) * a.S * row_words + h * (uint32_t)words +
+                          min(cl, words - 1);
   int32_t acc[4] = {0, 0, 0, 0};
   int64_t accw[4] = {0, 0, 0, 0};
   auto fetch = [&](uint32_t(&v)[CH][NC], int i0) {
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(256) void deform_group_kernel(DeformArgs a) {
     if (i0 + 2 * CH < LP) fetch(va, i0 + 2 * CH);
     if (second) use(vb, i0 + CH);
   }
-  if (!live) return;
+  if (!live || cl >= words) return;
   uint32_t packed = 0;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
@@ -339,7 +348,7 @@ __global__ __launch_bounds__(256) void deform_group_kernel(DeformArgs a) {
                                  : rq_bilinear(accw[c], a.out_mult, a.out_shift);
     packed |= (uint32_t)(rv & 0xff) << (8 * c);
   }
-  ((uint32_t*)a.out)[(int64_t)grp * G + cl] = packed;
+  ((uint32_t*)a.out)[(int64_t)grp * words + cl] = packed;
 }
 
 template <int MODE>
@@ -356,14 +365,19 @@ hipError_t launch_group(const DeformArgs& a, int32_t J, dim3 grid, hipStream_t s
 }  // namespace
 
 hipError_t launch_deform(const DeformArgs& a, hipStream_t s) {
-  const int64_t threads = (int64_t)a.B * a.Q * a.H * (a.Dh / 4);
-  if (threads == 0) return hipSuccess;
-  dim3 grid((unsigned)((threads + 255) / 256)), block(256);
-  const int32_t G = a.Dh / 4, LP = a.L * a.P, J = (LP + G - 1) / G;
-  // (group numbers and an image's word offsets are 32-bit there)
-  if (G >= 4 && G <= 64 && (G & (G - 1)) == 0 && J <= 4 &&
-      (int64_t)a.B * a.Q * a.H <= INT32_MAX && (int64_t)a.S * a.H * G <= UINT32_MAX)
+  const int64_t groups = (int64_t)a.B * a.Q * a.H;
+  if (groups == 0) return hipSuccess;
+  const int32_t words = a.Dh / 4, G = group_lanes(words), LP = a.L * a.P, J = (LP + G - 1) / G;
+  // The group kernel up to 4 samples a lane, where its threads and an image's
+  // word offsets are 32-bit.  It is the faster one also with idle lanes: 48
+  // channels per head on 16 lanes, 8 x 300 queries, 8 heads, 12 samples:
+  // nearest 7.6 us (the general kernel 25.8), boxes and bilinear 13.1
+  // (44.3).
+  if (J <= 4 && groups * G <= UINT32_MAX && (int64_t)a.S * a.H * words <= UINT32_MAX) {
+    const dim3 grid((unsigned)((groups * G + 255) / 256));
     return a.mode == 0 ? launch_group<0>(a, J, grid, s) : launch_group<1>(a, J, grid, s);
+  }
+  const dim3 grid((unsigned)((groups * words + 255) / 256)), block(256);
   hipLaunchKernelGGL(deform_kernel, grid, block, 0, s, a);
   return hipGetLastError();
 }

@@ -1456,8 +1456,8 @@ def test_deform_boxes_shapes(mode, P):
                                           (32, ((9, 13), (4, 6), (2, 3), (1, 1)), 8),  # 8 lanes, 4 each
                                           (64, ((7, 5),), 1),                  # 16 lanes, 1 each
                                           (256, ((6, 6), (3, 3)), 32),         # 64 lanes, 1 each
-                                          (8, ((5, 5),), 2),                   # 2 lanes: general kernel
-                                          (48, ((5, 4), (2, 2)), 3)])          # 12 lanes: general kernel
+                                          (8, ((5, 5),), 2),                   # 4 lanes, 2 of them idle
+                                          (48, ((5, 4), (2, 2)), 3)])          # 16 lanes, 4 of them idle
 def test_deform_lane_groups(mode, boxes, dh, levels, P):
     """Every way the sampler splits a (query, head) over lanes."""
     say(f"deform lane groups dh={dh} levels={levels} P={P} mode={mode} boxes={boxes}")
@@ -1472,6 +1472,25 @@ def test_deform_lane_groups(mode, boxes, dh, levels, P):
                      dev(d["offsets"]), dev(d["logits"]), d["I0"], d["out_mult"],
                      d["out_shift"], mode))
     assert_same(got, ref, "deform lane groups")
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("dh,P", [(4, 5), (20, 4), (48, 5), (144, 4), (256, 1),
+                                  (4, 6), (16, 6), (20, 11)])  # 5 samples a lane: general kernel
+def test_deform_idle_lanes(dh, P, mode):
+    """Head dimensions that fill no lane group (1, 5, 12 and 36 words on 4, 8,
+    16 and 64 lanes) and sample counts on both sides of the group kernel's
+    four per lane."""
+    say(f"deform idle lanes dh={dh} P={P} mode={mode}")
+    wl = synth.DeformWorkload("i", 2, 9, dh * 3, 3, dh, ((9, 13), (4, 6), (2, 3)), P)
+    d = synth.deform_inputs(wl, 80 + dh + P, boxes=True)
+    ref = oracle.deform_attn(d["value"], d["level_hw"], d["level_start"], d["ref"],
+                             d["offsets"], d["logits"], d["I0"], d["out_mult"],
+                             d["out_shift"], mode)
+    got = host(ilw.ilw_deform_attn_boxes(dev(d["value"]), d["level_hw"], d["level_start"],
+                                         dev(d["ref"]), dev(d["offsets"]), dev(d["logits"]),
+                                         d["I0"], d["out_mult"], d["out_shift"], mode))
+    assert_same(got, ref, "deform idle lanes")
 
 
 @pytest.mark.parametrize("mode", [0, 1])
@@ -1505,8 +1524,8 @@ def test_deform_shiftmax_params(smax, dh, boxes, mode):
     """Every Constrained Shiftmax parameter of the sampler away from the
     decoder's defaults: k_out down to 2 (weights 0 or 1), m_p = 31 with the
     per-row s_d (the output shift reaches the 64-bit cap), static s_d up to
-    31 with I0 at both ends of its range; the wave-group kernel (32 channels
-    per head) and the general one (48).  The output shift is the smallest in
+    31 with I0 at both ends of its range; lane groups with (48 channels per
+    head) and without (32) idle lanes.  The output shift is the smallest in
     [20, 40) at which the oracle saturates under a fifth of the outputs."""
     k_inter, k_out, m_p, s_d, I0 = smax
     say(f"deform smax k_inter={k_inter} k_out={k_out} m_p={m_p} s_d={s_d} I0={I0} "
