@@ -309,10 +309,14 @@ hipError_t launch_split_tile(const SplitArgs& a, hipStream_t s) {
 
 hipError_t launch_split_conv(const SplitArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;
-  // 32 x 32 per wave (the int64 running sums take 2 registers per output):
-  // 64 x 64 workgroups for small grids, 128 x 64 beyond.
+  // 32 x 32 per wave (the int64 running sums take 2 registers per output).
+  // 64 x 64 workgroups for small grids, and where at most four of them read
+  // the same tokens: 51 200 tokens of 3 x 192 channels to 256 32.9 us (128 x
+  // 64: 33.5), 25 600 tokens 18.2 (19.4), 51 200 of 2 x 192 to 128 15.3
+  // (16.4).  128 x 64 beyond: 25 200 tokens of 4 x 192 to 384 27.5 us (64 x
+  // 64: 27.8).
   const int64_t waves = ((a.M + 63) / 64) * ((a.N + 63) / 64) * 4;
-  if (waves <= 4096) return launch_split_tile<2, 2, 2, 2>(a, s);
+  if (waves <= 4096 || a.N <= 256) return launch_split_tile<2, 2, 2, 2>(a, s);
   return launch_split_tile<4, 2, 2, 2>(a, s);
 }
 
