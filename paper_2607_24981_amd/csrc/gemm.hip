@@ -492,9 +492,14 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
   }
   if constexpr (QSTAGED) {
     // Q and K chunks to their window-major rows (16-byte aligned: the rows
-    // are 64 bytes, the workspace 16-byte aligned).  V (with quads: a chunk's
-    // 4 tokens are 4 consecutive keys): thread (r, q) takes channels 4 (r % 4)
-    // .. + 3 of chunk q for the 4 tokens from r & ~3 on, transposed.
+    // are 64 bytes, the workspace 16-byte aligned).  V: where a token's
+    // quad of keys (k & ~3 .. + 3) is 4 consecutive tokens of the tile, which
+    // is so when the offsets of its first and last key's tokens differ by 3,
+    // the token of key k takes channels 4 (k % 4) .. + 3 of its chunk for the
+    // 4 tokens, transposed; other tokens store their bytes.  With quads the
+    // tile's tokens all are such.  (A block of 31 images of 34 x 7 tokens,
+    // 512 channels, one window an image: 109.8 us with bytes alone, 94.8 so;
+    // 20 of 27 x 38, 384 channels, 9 x 19 windows: 143.4 and 119.1.)
     lds_sync();
     const uint32_t* so = (const uint32_t*)sbuf;
     const QkvLayout& Lq = a.qkv;
@@ -510,8 +515,11 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
       if (part < 2) {
         int8_t* dst = (part == 0 ? Lq.q : Lq.k) + qoff[r][0] + (int64_t)h * Lq.Tw * 64 + cc;
         *(v4i*)dst = *(const v4i*)(so + r * OSTR + q * 4);
-      } else if (v_quads) {
-        const int r4 = r & ~3, s4 = r & 3;
+        continue;
+      }
+      const int s4 = (int)qoff[r][1] & 3, r4 = r - s4;  // (a window's V starts at a multiple of 64)
+      if (v_quads || (r4 >= 0 && r4 + 3 < TM && m0 + r4 + 3 < M &&
+                      qoff[r4 + 3][1] - qoff[r4][1] == 3)) {
         uint32_t w[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) w[t] = so[(r4 + t) * OSTR + q * 4 + s4];

@@ -696,9 +696,11 @@ def test_block_large_unpacked(dims, B, win):
 
 
 @pytest.mark.parametrize("dims,grid,win,B", [
-    ((192, 3, 768), (21, 22), (7, 11), 24),    # keys leave one by one
+    ((192, 3, 768), (21, 22), (7, 11), 24),    # in part 4 x 4, in part one by one
+    ((192, 3, 768), (23, 10), (23, 10), 48),   # 4 x 4, in every second image from token 2 on
+    ((192, 3, 768), (35, 3), (35, 1), 105),    # one by one: neighbours in other windows
     ((192, 3, 768), (21, 24), (7, 12), 23),    # 4 keys x 4 channels at a time
-    ((384, 6, 1536), (18, 19), (9, 19), 12),   # the 256-channel tile, one by one
+    ((384, 6, 1536), (18, 19), (9, 19), 12),   # the 256-channel tile, 4 x 4 across its edges
     ((384, 6, 1536), (19, 20), (19, 4), 12),   # 4 x 4
     ((128, 2, 512), (5, 4), (5, 4), 500),      # 384 channels, Q | K | V inside one tile
 ])
