@@ -9,7 +9,7 @@
 //   y  = Res(rq(g W2^T + b2), x1)               -> y   (the block's output)
 //   h' = LN1 of the next block (y)              -> y2  (optional)
 //
-// A workgroup holds 64 tokens (16 or 32 where the launch has few: see
+// A workgroup holds 64 tokens (16 where the launch has few: see
 // launch_tail384).  Each of its 12 waves owns 32 channels of all its tokens
 // in every 384-wide result (projection, each 384-channel chunk of fc1, fc2)
 // and loads its weight fragments from global memory straight into MFMA
@@ -486,8 +486,9 @@ hipError_t launch_tail384(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs
   if (!tail384_kernel_applies(fp.M, fp.N, f1.N) || fp.K != T_D || f1.K != T_D ||
       f2.K != f1.N || f2.N != T_D || !fp.wp || !f1.wp || !f2.wp)
     return hipErrorInvalidValue;
-  // Tokens per workgroup: the fewest that keep the grid within one workgroup
-  // per CU.  Up to there a launch takes as long as one workgroup, whose time
+  // 16 tokens per workgroup while that keeps the grid within one workgroup
+  // per CU, else 64.  (32 are faster up to 8192 tokens alone, but fill the
+  // CUs that half batches on two streams share.)  Up to there a launch takes as long as one workgroup, whose time
   // is its epilogues' VALU work (proportional to its tokens) above the weight
   // stream (1.3 MB through one CU whatever its tokens: 8.6 us at 64 bytes a
   // cycle); past it the smaller tiles only read the weights more often.
@@ -497,7 +498,6 @@ hipError_t launch_tail384(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs
   //   8192       67.2 / 54.9 / 59.4    12288       90.8 / 79.0 / 67.2
   //   16384     116.5 / 89.9 / 79.0    32768      207.8 / 156.1 / 139.0
   if (fp.M <= 16 * NCU) tail384_tile<1>(fp, f1, f2, layernorm, s);
-  else if (fp.M <= 32 * NCU) tail384_tile<2>(fp, f1, f2, layernorm, s);
   else tail384_tile<4>(fp, f1, f2, layernorm, s);
   return hipGetLastError();
 }
