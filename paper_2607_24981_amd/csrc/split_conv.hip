@@ -49,6 +49,21 @@ struct __attribute__((aligned(16))) BrChan {
   int32_t mult, shift;
 };
 
+// sat8(floor((t m + 2^(s-1)) / 2^s)) for any int64 t and s in [1, 62].  With
+// t = 2^32 hi + lo, p = lo m fits int64 and H = hi m + floor(p / 2^32) is
+// floor(t m / 2^32), below 2^63.  u = floor(t m / 2^(s-1)), of which
+// floor((u + 1) / 2) is the rounded value, is a shift of H where s > 32, and
+// otherwise of H and the low word of p: there |H| >= 2^9 saturates, so H is
+// clamped to that first.
+__device__ __forceinline__ int32_t rq_wide(int64_t t, int32_t mult, int32_t shift) {
+  const int64_t p = (int64_t)(uint32_t)t * mult;
+  const int64_t H = (t >> 32) * mult + (p >> 32);
+  const int64_t Hc = min(max(H, (int64_t)-512), (int64_t)511);
+  const int64_t u = shift > 32 ? H >> (shift - 33)
+                               : (Hc * ((int64_t)1 << 32) + (uint32_t)p) >> (shift - 1);
+  return sat8((u + 1) >> 1);
+}
+
 template <int WN, int WM, int FI, int FJ, int PF>
 __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, int32_t tiles_n,
                                                                  int64_t tiles_total) {
@@ -219,6 +234,8 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
 
   sstore(0, 0);
   wide = __syncthreads_or(wide);
+  if (wide)  // the addend is then the bias alone (published by the K loop's barriers)
+    for (int c = tid; c < TN; c += NT) rqc[c].c = a.bias ? a.bias[min(n0 + c, N - 1)] : 0;
   gload(0);
   int b = 0, ck = 0, csteps = a.C[0] / TK;  // branch of the current step, its steps
   for (int s0 = 0; s0 < S; s0 += PF) {
@@ -241,8 +258,7 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
   }
 
   // Epilogue: output requantization, from int32 sums by the staged constants;
-  // where a sum may be larger (wide) it is first clamped to the channel's
-  // saturation bound.
+  // where a sum may be larger (wide) through the 95-bit product.
   auto put = [&](int i, int j, int32_t n, const int32_t(&v)[4]) {
     ((uint32_t*)sbuf)[(wm * WTM + j * 16 + (lane & 15)) * OSTR + ((n - n0) >> 2)] =
         pack4(v[0], v[1], v[2], v[3]);
@@ -267,12 +283,8 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
         int32_t v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int32_t nn = min(n + r, N - 1), q = a.onq == 1 ? 0 : nn;
-          ChanRq cr;
-          cr.init(a.omult[q], a.oshift[q], 0);
-          int64_t t = tot[i][j][r] + (a.bias ? a.bias[nn] : 0);
-          t = t < -(int64_t)cr.L ? -(int64_t)cr.L : (t > cr.L ? cr.L : t);
-          v[r] = cr.apply((int32_t)t);
+          const RqI64 q = rqc[n - n0 + r];
+          v[r] = rq_wide(tot[i][j][r] + q.c, q.mult, q.shift);
         }
         put(i, j, n, v);
       }

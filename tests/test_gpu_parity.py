@@ -1308,6 +1308,30 @@ def test_split_conv_edge_params():
     assert_same(_split_gpu(xs, ws, bm, bs, None, om, os_), ref, "split conv ties")
 
 
+@pytest.mark.parametrize("branch", [((1 << 31) - 1, 1), (3 << 28, 12), ((1 << 30) + 1, 19)])
+def test_split_conv_wide_sums(branch):
+    """Sums far outside int32 (to 2^52, 2^38 and 2^33) whose requantized values
+    are not saturated: small output multipliers, large output shifts."""
+    say(f"split conv wide sums branch={branch}")
+    g = rng(79)
+    M, N, C = 66, 128, 192
+    x = g.integers(-127, 128, (M, C)).astype(np.int8)
+    x[0], x[1] = 127, -127
+    w = g.integers(-127, 128, (N, C)).astype(np.int8)
+    w[::3] = 127
+    b = g.integers(-2 ** 31, 2 ** 31, N).astype(np.int32)
+    # |sum m / 2^s| about 2^6 at the largest sum of 192 * 127^2
+    top = 192 * 127 * 127 * branch[0] >> branch[1]
+    os_ = g.integers(1, 63, N).astype(np.int32)
+    om = np.array([max(1, min(2 ** 31 - 1, (64 << int(v)) // top)) for v in os_])
+    om = (om * g.choice([-1, 1], N)).astype(np.int32)
+    args = ([x], [w], [np.full(1, branch[0], np.int32)], [np.full(1, branch[1], np.int32)], b, om,
+            os_)
+    ref = oracle.split_conv(*args)
+    assert np.mean((np.abs(ref) < 127) & (ref != 0)) > 0.2
+    assert_same(_split_gpu(*args), ref, "split conv wide sums")
+
+
 def _offset_output(shape, off=4):
     """A poisoned device buffer and a view into it at a 4-byte (not 16-byte)
     aligned offset, for outputs that only need 4-byte alignment."""

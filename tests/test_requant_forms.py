@@ -120,6 +120,41 @@ def test_linear_clamp_is_needed():
     assert rq_linear(acc, 0, m, s) == rq_exact(acc, m, s) == 127
 
 
+# ---------------------------------------------------- wide split-convolution sums
+def rq_wide(t, m, s):
+    """The split convolution's requantization of a 64-bit sum through the two
+    halves of t: u = floor(t m / 2^(s-1)), rounded by (u + 1) >> 1."""
+    p = (t & 0xffffffff) * m
+    h = (t >> 32) * m + (p >> 32)
+    assert in_range(p, I64) and in_range(h, I64), "int64 overflow"
+    if s > 32:
+        u = h >> (s - 33)
+    else:
+        hc = max(-512, min(511, h))
+        u = ((hc << 32) + (p & 0xffffffff)) >> (s - 1)
+    assert in_range(u + 1, I64), "int64 overflow"
+    return max(-127, min(127, (u + 1) >> 1))
+
+
+def test_wide_sum_form_is_exact():
+    """Every shift, multipliers from 1 to 2^31 - 1 of both signs, sums at every
+    rounding and saturation boundary that int64 holds and at its ends."""
+    rng = np.random.default_rng(9)
+    for s in range(1, 63):
+        for m in [1, -1, 3, (1 << 31) - 1, 1 - (1 << 31), -(1 << 30),
+                  *(int(v) for v in rng.integers(-(1 << 31) + 1, 1 << 31, 3)), 0]:
+            ts = {0, 1, -1, *I64, 1 << 32, (1 << 32) - 1, -(1 << 32)}
+            ts.update(int(v) >> int(k) for v, k in zip(rng.integers(*I64, 20),
+                                                       rng.integers(0, 40, 20)))
+            if m:
+                for q in [-512, -129, -128, -127, -126, -1, 0, 1, 126, 127, 128, 511, 512]:
+                    t = math.floor(Fraction((2 * q + 1) << s, 2 * m))
+                    ts.update({t - 1, t, t + 1, t + 2})
+            for t in ts:
+                if in_range(t, I64):
+                    assert rq_wide(t, m, s) == rq_exact(t, m, s), (t, m, s)
+
+
 # ------------------------------------------------------------ 64-bit score form
 def rq_score_fast(acc, m, s):
     x = acc * m + (1 << (s - 1)) + (128 << s)
