@@ -172,7 +172,8 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
       brc[b][c] = {(int64_t)1 << (sh - 1), a.bmult[b][q], sh};
     }
   // The output requantization once per channel, and whether every channel's
-  // sum of rescaled partials stays inside int32: |acc_b| <= C_b 2^14, so
+  // sum of rescaled partials stays inside int32 and, with its bias, below the
+  // 3 * 2^30 that RqI64 is exact for: |acc_b| <= C_b 2^14, so
   // |r_b| <= C_b 2^14 |m_b| / 2^s_b + 1 (sums of up to 8 terms below 2^61).
   int wide = 0;
   for (int c = tid; c < TN; c += NT) {
@@ -183,10 +184,11 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
       const int64_t m = a.bmult[b][q];
       bound += (((int64_t)a.C[b] << 14) * (m < 0 ? -m : m) >> a.bshift[b][q]) + 1;
     }
-    wide |= bound > INT32_MAX;
+    const int32_t bias = a.bias ? a.bias[n] : 0;
+    wide |= bound > INT32_MAX || bound + llabs((int64_t)bias) >= ((int64_t)3 << 30);
     const int32_t q = a.onq == 1 ? 0 : n;
     RqI64 r;
-    r.init(a.omult[q], a.oshift[q], a.bias ? a.bias[n] : 0);
+    r.init(a.omult[q], a.oshift[q], bias);
     rqc[c] = r;
   }
 

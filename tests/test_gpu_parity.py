@@ -1332,6 +1332,29 @@ def test_split_conv_wide_sums(branch):
     assert_same(_split_gpu(*args), ref, "split conv wide sums")
 
 
+@pytest.mark.parametrize("bias", [0, 1610612734, 1610612735, (1 << 31) - 1])
+def test_split_conv_sum_and_bias_limits(bias):
+    """Sums of rescaled partials near int32's end with biases up to int32's
+    end on either side of them, and output multipliers and shifts at which
+    nothing clamps the sum: |sum + bias| is below 3 * 2^30 for the first two
+    biases (192 * 2^14 * 2^9 + 1 bounds the sum), from there on at or above
+    it."""
+    say(f"split conv sum and bias limits bias={bias}")
+    g = rng(78)
+    M, N, C = 66, 64, 192
+    x = np.full((M, C), 127, np.int8)
+    x[1::2] = -127
+    x[6:] = g.integers(-127, 128, (M - 6, C))
+    w = np.full((N, C), 127, np.int8)
+    sign = np.where(np.arange(N) % 2 == 0, 1, -1)
+    b = (bias * sign).astype(np.int32)
+    om = (np.array([(1 << 31) - 1, (1 << 31) - 1, 1 << 30, 3])[np.arange(N) % 4] *
+          np.where(np.arange(N) % 8 < 4, 1, -1)).astype(np.int32)
+    os_ = np.array([62, 58, 55, 54, 53, 40, 20, 1], np.int32)[np.arange(N) // 8]
+    args = ([x], [w], [np.full(1, 1 << 30, np.int32)], [np.full(1, 21, np.int32)], b, om, os_)
+    assert_same(_split_gpu(*args), oracle.split_conv(*args), "split conv sum and bias limits")
+
+
 def _offset_output(shape, off=4):
     """A poisoned device buffer and a view into it at a 4-byte (not 16-byte)
     aligned offset, for outputs that only need 4-byte alignment."""

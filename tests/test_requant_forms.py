@@ -111,6 +111,23 @@ def test_linear_form_random_parameters():
             assert rq_linear(acc, b, m, s) == rq_exact(acc + b, m, s), (acc, b, m, s)
 
 
+def test_linear_form_domain():
+    """The form holds for |acc + b| < 3 * 2^30, past int32, whatever the
+    multiplier and shift (the split convolution adds int32 biases to sums that
+    fill int32); at 2^32 the largest multiplier with a shift that needs no clamp
+    leaves int64."""
+    rng = np.random.default_rng(10)
+    top = (3 << 30) - 1
+    for s in range(1, 63):
+        for m in [(1 << 31) - 1, -(1 << 30), 1, *(int(v) for v in rng.integers(1, 1 << 31, 4))]:
+            for b in [(1 << 31) - 1, -(1 << 31), 1 << 30, 0]:
+                for acc in [*I32, 0, top - b, -top - b, *(int(v) for v in rng.integers(*I32, 4))]:
+                    if in_range(acc, I32) and abs(acc + b) <= top:
+                        assert rq_linear(acc, b, m, s) == rq_exact(acc + b, m, s), (acc, b, m, s)
+    with pytest.raises(AssertionError, match="int64 overflow"):
+        rq_linear((1 << 31) - 2, (1 << 31) - 1, (1 << 31) - 1, 55)
+
+
 def test_linear_clamp_is_needed():
     """Without the clamp a small shift with a large multiplier leaves int32
     after the shift (m = 2^31 - 1, s = 1, acc = 2^24 gives about 2^54)."""
