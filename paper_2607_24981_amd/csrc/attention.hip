@@ -52,23 +52,26 @@ constexpr int full_slots(int nb) { return nb <= 10 ? nb : nb <= 12 ? 10 : nb <= 
 // The scores are kept complemented, n = ~q = -q - 1 in [-128, 126]: the row
 // maximum of q is the row minimum of n, and max - q = n - min.
 //   ~floor((acc m + r) / 2^s) = floor((-acc m - r - 1) / 2^s),
-// so with nm = -m and c = -2^(s-1) - 1 the complement costs nothing.  For s in
-// [32, 54] the shift is one of the product's high word: |acc| <= 2^20 for a
-// 64-channel head and |m| < 2^31, so the 64-bit sum is exact and the shifted
-// high word is the value itself.
-__device__ __forceinline__ int32_t score_fast(int32_t acc, int32_t nm, int64_t c, int32_t s32) {
-  const int32_t v = (int32_t)(((int64_t)acc * nm + c) >> 32) >> s32;
+// so with nm = -m and c = -2^(s-1) - 1 the complement costs nothing.
+// |acc| <= 2^20 for a 64-channel head, |m| < 2^31 and s in [22, 54]
+// (launch_attention) keep the 64-bit sum exact and the result inside int32.
+// From 32 on the shift is one of the sum's high word, below it is the low word
+// of the 64-bit shift: one instruction each.
+template <bool HIGH>
+__device__ __forceinline__ int32_t score(int32_t acc, int32_t nm, int64_t c, int32_t s) {
+  const int64_t p = (int64_t)acc * nm + c;
+  const int32_t v = HIGH ? (int32_t)(p >> 32) >> (s - 32)
+                         : (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, s);
   return min(max(v, ~kQmax), ~kQmin);
 }
 
-// Otherwise (any s in [1, 62]) the accumulator is clamped to [-L, L] first:
-// that keeps every saturated result saturated and the shifted value inside
-// int32.
-__device__ __forceinline__ int32_t score_clamped(int32_t acc, int32_t L, int32_t mult,
-                                                 int64_t rnd, int32_t shift) {
-  acc = min(max(acc, -L), L);
-  const int64_t v = ((int64_t)acc * mult + rnd) >> shift;
-  return ~min(max((int32_t)v, kQmin), kQmax);
+// Either, for one more instruction: with k = max(32 - s, 0), acc, c and the
+// shift are scaled by 2^k first, |acc| 2^k <= 2^30.
+__device__ __forceinline__ int32_t score_any(int32_t acc, int32_t k, int32_t nm, int64_t ck,
+                                             int32_t s32) {
+  const int32_t v =
+      (int32_t)(((int64_t)(int32_t)((uint32_t)acc << k) * nm + ck) >> 32) >> s32;
+  return min(max(v, ~kQmax), ~kQmin);
 }
 
 // Ends a step of an unrolled loop: neither loads nor arithmetic move across,
@@ -103,9 +106,10 @@ struct SumType<true> {
 // R query rows (16 or 32) per workgroup of NW waves; wave w takes the 16-key
 // blocks w, w + NW, ... : NB slots, of which only the last can be missing or
 // partial (NB = ceil(blocks / NW)).  FAST: the host has shown (launch_attention)
-// that the scores take the high-word form, that a wave's sum of a row's 16 NB
-// exponentials stays below 2^32, and that P is one multiply without a clamp.
-template <int R, int NW, int NB, bool FAST>
+// that a wave's sum of a row's 16 NB exponentials stays below 2^32, and that P
+// is one multiply without a clamp; HIGH then says which way the scores are
+// shifted.
+template <int R, int NW, int NB, bool FAST, bool HIGH>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
   constexpr int NF = R / 16;                      // query fragments of 16 rows
@@ -192,9 +196,11 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
   int32_t mn[NF];
 #pragma unroll
   for (int f = 0; f < NF; ++f) mn[f] = ~kQmin;
-  auto phase1 = [&](auto fast) {
-    const int32_t nm = -a.score_mult, s32 = a.score_shift - 32;
-    const int64_t rnd = (int64_t)1 << (a.score_shift - 1), c = -rnd - 1;
+  {
+    const int32_t nm = -a.score_mult, ss = a.score_shift;
+    const int64_t c = -((int64_t)1 << (ss - 1)) - 1;
+    const int32_t k = max(32 - ss, 0), s32 = max(ss - 32, 0);
+    const int64_t ck = c * ((int64_t)1 << k);
     v4i pr[2][NF];  // products, alternating
     auto products = [&](int j) {
 #pragma unroll
@@ -208,10 +214,8 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
         int32_t n[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          n[r] = decltype(fast)::value
-                     ? score_fast(pr[j & 1][f][r], nm, c, s32)
-                     : score_clamped(pr[j & 1][f][r], a.score_clamp, a.score_mult, rnd,
-                                     a.score_shift);
+          n[r] = FAST ? score<HIGH>(pr[j & 1][f][r], nm, c, ss)
+                      : score_any(pr[j & 1][f][r], k, nm, ck, s32);
         mn[f] = min(min(mn[f], n[0]), n[1]);
         mn[f] = min(min(mn[f], n[2]), n[3]);
         if (j < NBF) {
@@ -231,14 +235,6 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
       emit(j);
       step_end(mn[0], mn[NF - 1]);
     }
-  };
-  if constexpr (FAST) {
-    phase1(Flag<true>{});
-  } else {
-    if (a.rq_fast)
-      phase1(Flag<true>{});
-    else
-      phase1(Flag<false>{});
   }
   // row minima: combine the 4 lanes sharing a row, then the waves
 #pragma unroll
@@ -521,12 +517,12 @@ __global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, Qk
   }
 }
 
-template <int R, int NW, int NB, bool FAST>
+template <int R, int NW, int NB, bool FAST, bool HIGH = true>
 hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
   const uint32_t nrb = (uint32_t)(a.Tw + R - 1) / R;
   const uint32_t ntiles = nrb * (uint32_t)(a.H * a.B * a.nW);
-  hipLaunchKernelGGL((attention_kernel<R, NW, NB, FAST>), dim3(ntiles), dim3(64 * NW), 0, s, a,
-                     nrb, ntiles);
+  hipLaunchKernelGGL((attention_kernel<R, NW, NB, FAST, HIGH>), dim3(ntiles), dim3(64 * NW), 0, s,
+                     a, nrb, ntiles);
   return hipGetLastError();
 }
 
@@ -537,9 +533,10 @@ hipError_t launch_slots(const AttnArgs& a, int32_t nb, bool fast, hipStream_t s)
     if (nb > LO) return launch_slots<R, NW, LO + 1, HI>(a, nb, fast, s);
   }
   // 32-bit sums over a wave's keys are exact while 16 nb ShiftExp(0) < 2^32
-  return fast && (((int64_t)a.I0 << a.k_inter) * 16 * LO < ((int64_t)1 << 32))
-             ? launch_variant<R, NW, LO, true>(a, s)
-             : launch_variant<R, NW, LO, false>(a, s);
+  if (!fast || ((int64_t)a.I0 << a.k_inter) * 16 * LO >= ((int64_t)1 << 32))
+    return launch_variant<R, NW, LO, false>(a, s);
+  return a.score_shift >= 32 ? launch_variant<R, NW, LO, true, true>(a, s)
+                             : launch_variant<R, NW, LO, true, false>(a, s);
 }
 
 // Whether P = floor(e F / 2^sh) is one high-word multiply for every row of n
@@ -576,22 +573,31 @@ int32_t clamp_bound(int64_t am, int32_t shift) {
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   if (a.B == 0) return hipSuccess;
   AttnArgs b = a;
-  // A score multiplier with room to spare takes a larger shift (the same
-  // value m / 2^s, so the same rounding), which reaches the high-word form.
+  // Every score scale m / 2^s as one with s in [22, 54] and the same results,
+  // |acc| <= 2^20.  A multiplier with room to spare takes a larger shift up to
+  // 32 (the same value, so the same rounding), where the shift is that of the
+  // product's high word.  One that stops short of 22 is at least 2^30: acc = 0
+  // gives 0 and any other saturates, as with 2^30 / 2^22.  Past 54 every score
+  // rounds to 0: |acc m| < 2^51.
   int64_t am = a.score_mult < 0 ? -(int64_t)a.score_mult : (int64_t)a.score_mult;
   while (b.score_shift < 32 && am < ((int64_t)1 << 30)) {
     b.score_mult *= 2;
     b.score_shift += 1;
     am *= 2;
   }
-  b.score_clamp = clamp_bound(am, b.score_shift);
+  if (b.score_shift < 22) {
+    b.score_mult = b.score_mult < 0 ? -(1 << 30) : 1 << 30;
+    b.score_shift = 22;
+  } else if (b.score_shift > 54) {
+    b.score_mult = 0;
+    b.score_shift = 54;
+  }
   b.pv_clamp = clamp_bound(a.pv_mult < 0 ? -(int64_t)a.pv_mult : (int64_t)a.pv_mult, a.pv_shift);
-  b.rq_fast = b.score_shift >= 32 && b.score_shift <= 54;
   b.inv_ww = 1.0f / (float)a.win_w;
   // floor(z / I0) = umulhi(z, ceil(2^32 / I0)) for z <= k_inter I0 <= 16 I0:
   // the excess z (I0 ceil(2^32 / I0) - 2^32) < 16 I0^2 <= 2^32
   b.inv_I0 = a.I0 == 1 ? 0 : (uint32_t)((((uint64_t)1 << 32) + a.I0 - 1) / (uint32_t)a.I0);
-  const bool fast = b.rq_fast && p_fast(a, a.Tw);
+  const bool fast = p_fast(a, a.Tw);
   const int32_t nkb = (a.Tw + 15) >> 4;  // 16-key blocks
   const int64_t wg32 = (int64_t)((a.Tw + 31) / 32) * a.H * a.B * a.nW;
   if (nkb <= 32) {

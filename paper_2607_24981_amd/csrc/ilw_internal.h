@@ -559,9 +559,9 @@ struct AttnArgs {
   int32_t B, T, D, H, grid_w, win_h, win_w, nwx, nW, Tw, Twp;
   int32_t score_mult, score_shift, I0, k_inter, k_out, m_p, s_d, pv_mult, pv_shift;
   int32_t hd;        // head dimension: 32 or 64
-  // set by launch_attention: the scores take the high-word form, accumulator
-  // clamps of the two requantizations, reciprocals
-  int32_t rq_fast, score_clamp, pv_clamp;
+  // set by launch_attention: accumulator clamp of the output requantization,
+  // reciprocals
+  int32_t pv_clamp;
   uint32_t inv_I0;
   float inv_ww;
 };

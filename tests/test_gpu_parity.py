@@ -510,21 +510,25 @@ def test_attention_slots(T, windows, I0, s_d):
     assert_same(got, ref, "attention slots")
 
 
-# (score_mult, score_shift): the unclamped score form covers shifts 32..54,
-# and smaller shifts when |acc * m / 2^s| stays inside int32 (|acc| <= 2^20);
-# the rest clamp the accumulator first.
+# (score_mult, score_shift): multipliers below 2^30 are scaled up until the
+# shift reaches 32, and a shift still below 22 or above 54 is replaced; from 32
+# on the score is taken from the product's high word, below from its low word.
 SCORE_RQ = [
-    (1, 13),                      # unclamped: acc / 2^13, exact ties at acc = 4096 mod 8192
-    ((1 << 30) - 12345, 43),      # unclamped, shift >= 32
-    (-((1 << 29) + 5), 40),       # unclamped, negative scale
-    ((1 << 20) + 7, 22),          # unclamped below 32, mostly saturated
-    ((1 << 30) + 1, 31),          # unclamped at the largest shift below 32
-    ((1 << 30) + 1, 44),          # unclamped
-    ((1 << 31) - 1, 54),          # unclamped at its largest shift: every score rounds to 0
-    ((1 << 31) - 1, 32),          # unclamped at shift 32, mostly saturated
-    (-((1 << 31) - 1), 55),       # clamped: past 54
-    ((1 << 31) - 1, 62),          # clamped at the largest shift
-    (1 << 30, 12),                # clamped: the shifted value would overflow int32
+    (1, 13),                      # scaled to shift 32; exact ties at acc = 4096 mod 8192
+    ((1 << 30) - 12345, 43),      # high word
+    (-((1 << 29) + 5), 40),       # high word, negative scale
+    ((1 << 20) + 7, 22),          # scaled to shift 32, mostly saturated
+    ((1 << 30) + 1, 31),          # low word, the largest shift
+    (-((1 << 31) - 1), 30),       # low word, negative scale
+    (-((1 << 29) + 5), 30),       # low word, scaled to shift 31
+    ((1 << 31) - 1, 22),          # low word, the smallest shift
+    (1 << 29, 20),                # below 22 after scaling: every score but 0 saturates
+    ((1 << 30) + 1, 44),          # high word
+    ((1 << 31) - 1, 54),          # high word, the largest shift: every score rounds to 0
+    ((1 << 31) - 1, 32),          # high word, the smallest shift, mostly saturated
+    (-((1 << 31) - 1), 55),       # replaced: past 54
+    ((1 << 31) - 1, 62),          # replaced: the largest shift
+    (1 << 30, 12),                # replaced: below 22
 ]
 
 
@@ -543,6 +547,28 @@ def test_attention_score_requant_paths(case, rqp):
                                      p["pv_mult"], p["pv_shift"]) for b in range(B)])
     got = host(ilw.ilw_attention(dev(qkv), gh, gw, wh, ww, H, p))
     assert_same(got, ref, "attention score requant")
+
+
+@pytest.mark.parametrize("case", [(1, 40, 40, 0, 0, 1), (2, 10, 10, 5, 5, 2), (1, 23, 23, 0, 0, 2)])
+@pytest.mark.parametrize("smax_I0", [16, 2000])
+@pytest.mark.parametrize("rqp", [((1 << 30) + 1, 31), (-((1 << 31) - 1), 30), ((1 << 29) + 5, 29),
+                                 ((1 << 30) + 7, 27), ((1 << 31) - 1, 23), (1 << 29, 20)])
+def test_attention_score_shifts_below_32(case, smax_I0, rqp):
+    """Queries and keys of -2 .. 2, whose sums of 64 products lie on both sides
+    of saturation at these scales (1/2 to 256 per unit), with exact ties."""
+    B, gh, gw, wh, ww, H = case
+    sm, ss = rqp
+    say(f"attention score shifts m={sm} s={ss} I0={smax_I0} B={B} grid={gh}x{gw} heads={H}")
+    g = rng(ss * 5 + gh)
+    D, T = 64 * H, gh * gw
+    qkv = g.integers(-2, 3, (B, T, 3 * D)).astype(np.int8)
+    qkv[..., 2 * D:] = g.integers(-127, 128, (B, T, D))
+    p = {"score_mult": sm, "score_shift": ss, "smax_I0": smax_I0, "smax_s_d": -1,
+         "pv_mult": (1 << 29) + 77, "pv_shift": 35}
+    ref = np.stack([oracle.attention(qkv[b], gh, gw, wh, ww, H, 64, sm, ss, smax_I0,
+                                     p["pv_mult"], p["pv_shift"]) for b in range(B)])
+    assert_same(host(ilw.ilw_attention(dev(qkv), gh, gw, wh, ww, H, p)), ref,
+                "attention score shifts")
 
 
 @pytest.mark.parametrize("case", [(1, 1, 300, 0, 0, 8), (2, 6, 10, 3, 5, 4),

@@ -173,17 +173,33 @@ def test_wide_sum_form_is_exact():
 
 
 # ------------------------------------------------------------ 64-bit score form
+def score_scale(m, s):
+    """The host's form of a score scale m / 2^s: a shift in [22, 54]."""
+    while s < 32 and abs(m) < 1 << 30:
+        m, s = 2 * m, s + 1
+    if s < 22:
+        return (-(1 << 30) if m < 0 else 1 << 30), 22
+    return (0, 54) if s > 54 else (m, s)
+
+
+def int32_word(v):
+    return ((v + (1 << 31)) % (1 << 32)) - (1 << 31)
+
+
 def rq_score_fast(acc, m, s):
-    x = acc * m + (1 << (s - 1)) + (128 << s)
-    assert -(1 << 63) <= x < 1 << 63, "int64 overflow"
-    v = x >> s                                     # arithmetic shift
-    lo = ((v + (1 << 31)) % (1 << 32)) - (1 << 31)  # the low word as int32
-    return max(1, min(255, lo)) - 128
-
-
-def score_fast_ok(m, s):
-    """The host's condition for the unclamped form."""
-    return s <= 54 and (s >= 32 or ((abs(m) << 20) >> s) + 257 < 1 << 31)
+    """A score by the kernel's one-shift form (the high word of the product
+    from shift 32 on, the low word of its 64-bit shift below), checked against
+    its form for either.  Scores are kept complemented: n = -q - 1."""
+    c = -(1 << (s - 1)) - 1
+    x = acc * -m + c
+    assert in_range(x, I64), "int64 overflow"
+    v = (x >> 32) >> (s - 32) if s >= 32 else int32_word(x >> s)
+    k = max(32 - s, 0)
+    xk = (acc << k) * -m + (c << k)
+    assert in_range(acc << k, I32) and in_range(xk, I64), "scaled form: overflow"
+    n, nk = (max(-128, min(126, w)) for w in (v, (xk >> 32) >> max(s - 32, 0)))
+    assert n == nk, (acc, m, s)
+    return ~n
 
 
 def score_cases(m, s, rng, n=400):
@@ -206,32 +222,29 @@ SCORE_PARAMS = [(1, 13), (3, 1), (1 << 29, 30), ((1 << 30) + 1, 31), (-(1 << 30)
 
 @pytest.mark.parametrize("m,s", SCORE_PARAMS)
 def test_score_fast_form_is_exact(m, s):
-    assert score_fast_ok(m, s)
     rng = np.random.default_rng(abs(m) % 997 + s)
     for acc in score_cases(m, s, rng):
-        assert rq_score_fast(acc, m, s) == rq_exact(acc, m, s), (acc, m, s)
+        assert rq_score_fast(acc, *score_scale(m, s)) == rq_exact(acc, m, s), (acc, m, s)
 
 
 def test_score_fast_random_parameters():
+    """Every shift, multipliers from 0 to 2^31 - 1 of both signs."""
     rng = np.random.default_rng(8)
-    n = 0
-    while n < 80:
-        s = int(rng.integers(1, 55))
-        m = int(rng.integers(-(1 << 31) + 1, 1 << 31))
-        if not score_fast_ok(m, s):
-            continue
-        n += 1
-        for acc in score_cases(m, s, rng, n=50):
-            assert rq_score_fast(acc, m, s) == rq_exact(acc, m, s), (acc, m, s)
+    for s in range(1, 63):
+        for m in [0, 1, -1, (1 << 31) - 1, 1 - (1 << 31), 1 << 30, -(1 << 30), (1 << 29) + 1,
+                  *(int(v) >> int(k) for v, k in zip(rng.integers(-(1 << 31) + 1, 1 << 31, 4),
+                                                     rng.integers(0, 31, 4)))]:
+            m2, s2 = score_scale(m, s)
+            assert 22 <= s2 <= 54 and abs(m2) < 1 << 31
+            for acc in score_cases(m, s, rng, n=30):
+                assert rq_score_fast(acc, m2, s2) == rq_exact(acc, m, s), (acc, m, s)
 
 
 def test_score_fast_condition_is_needed():
-    """Below s = 32 a large multiplier pushes the shifted value past int32:
-    m = 2^30, s = 12 and acc = 2^20 give 2^38, whose low word is 0 (a
-    wrong score of -128 before the clamp), so the host clamps the
-    accumulator first; past s = 54 the int64 sum itself overflows."""
-    assert not score_fast_ok(1 << 30, 12)
-    assert rq_score_fast(1 << 20, 1 << 30, 12) != rq_exact(1 << 20, 1 << 30, 12)
-    assert not score_fast_ok(1, 55)
+    """Scales that the host replaces would fail as they stand: m = 2^30, s = 12
+    and acc = 2^20 give 2^38, whose low word is 0, and past s = 54 the int64
+    sum overflows."""
+    assert int32_word((((1 << 20) * -(1 << 30)) - (1 << 11) - 1) >> 12) == -1
+    assert rq_exact(1 << 20, 1 << 30, 12) == 127
     with pytest.raises(AssertionError, match="overflow"):
-        rq_score_fast(1 << 20, (1 << 31) - 1, 56)
+        rq_score_fast(1 << 20, (1 << 31) - 1, 64)
