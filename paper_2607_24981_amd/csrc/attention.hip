@@ -94,22 +94,34 @@ __device__ __forceinline__ uint32_t pack_bytes(uint32_t a, uint32_t b, uint32_t 
   return lo | (hi << 16);
 }
 
-template <bool FAST>
+// How P = min(floor(e F / 2^sh), cap) is made, from what the host can show for
+// every row (p_form, launch_slots):
+//   P_MUL    the high word of one multiply; 32-bit sums over a wave's keys of a row
+//   P_SHIFT  that and a 32-bit shift; 32-bit sums over a lane's keys of a row
+//   P_ANY    64-bit products and sums, clamped
+// 8 images of 6 heads of 1600 keys take 58.0, 62.1 and 67.2 us (one general
+// instance for the last two, which spilled 28 registers, 71.0 us).
+enum PForm { P_MUL, P_SHIFT, P_ANY };
+
+template <PForm P>
 struct SumType {
-  typedef uint64_t type;
+  typedef uint32_t lane;
+  typedef uint64_t row;
 };
 template <>
-struct SumType<true> {
-  typedef uint32_t type;
+struct SumType<P_MUL> {
+  typedef uint32_t lane, row;
+};
+template <>
+struct SumType<P_ANY> {
+  typedef uint64_t lane, row;
 };
 
 // R query rows (16 or 32) per workgroup of NW waves; wave w takes the 16-key
 // blocks w, w + NW, ... : NB slots, of which only the last can be missing or
-// partial (NB = ceil(blocks / NW)).  FAST: the host has shown (launch_attention)
-// that a wave's sum of a row's 16 NB exponentials stays below 2^32, and that P
-// is one multiply without a clamp; HIGH then says which way the scores are
-// shifted.
-template <int R, int NW, int NB, bool FAST, bool HIGH>
+// partial (NB = ceil(blocks / NW)).  HIGH: how P_MUL and P_SHIFT shift the
+// scores (P_ANY, for parameters that no calibration gives, takes any shift).
+template <int R, int NW, int NB, PForm P, bool HIGH>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4)))
 void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
   constexpr int NF = R / 16;                      // query fragments of 16 rows
@@ -121,7 +133,8 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
   constexpr int TAB = 256 * kRow;
   __shared__ __attribute__((aligned(1024))) int8_t sbuf[PARTS * 16 > TAB ? PARTS * 16 : TAB];
   __shared__ __attribute__((aligned(16))) int32_t pmin[R][NW];
-  typedef typename SumType<FAST>::type Sum;
+  typedef typename SumType<P>::lane LaneSum;
+  typedef typename SumType<P>::row Sum;
   __shared__ __attribute__((aligned(16))) Sum psum[R][NW];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -214,8 +227,8 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
         int32_t n[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          n[r] = FAST ? score<HIGH>(pr[j & 1][f][r], nm, c, ss)
-                      : score_any(pr[j & 1][f][r], k, nm, ck, s32);
+          n[r] = P == P_ANY ? score_any(pr[j & 1][f][r], k, nm, ck, s32)
+                            : score<HIGH>(pr[j & 1][f][r], nm, c, ss);
         mn[f] = min(min(mn[f], n[0]), n[1]);
         mn[f] = min(min(mn[f], n[2]), n[3]);
         if (j < NBF) {
@@ -263,7 +276,7 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
     }
   };
   {
-    Sum sum[NF];
+    LaneSum sum[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       int32_t m = pmin[f * 16 + (lane & 15)][0];
@@ -304,17 +317,17 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
       }
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
+      Sum t = sum[f];
 #pragma unroll
       for (int o = 16; o < 64; o <<= 1) {
-        if (!FAST) {
-          const uint32_t lo = __shfl_xor((uint32_t)sum[f], o, 64);
-          const uint32_t hi = __shfl_xor((uint32_t)((uint64_t)sum[f] >> 32), o, 64);
-          sum[f] += (Sum)(((uint64_t)hi << 32) | lo);
-        } else {
-          sum[f] += __shfl_xor((uint32_t)sum[f], o, 64);
-        }
+        const uint32_t lo = __shfl_xor((uint32_t)t, o, 64);
+        // (32-bit lane sums have no high word yet at the first exchange)
+        const uint32_t hi = sizeof(Sum) == 8 && (sizeof(LaneSum) == 8 || o > 16)
+                                ? __shfl_xor((uint32_t)((uint64_t)t >> 32), o, 64)
+                                : 0;
+        t += (Sum)(((uint64_t)hi << 32) | lo);
       }
-      if (lane < 16) psum[f * 16 + lane][wave] = sum[f];
+      if (lane < 16) psum[f * 16 + lane][wave] = t;
     }
   }
   lds_sync();
@@ -336,16 +349,11 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
     sh = min(32 - a.k_out + sd, 63);
   }
   // With sh < 32 and F < 2^sh, Fs = F 2^(32-sh) fits in 32 bits and
-  // floor(e F / 2^sh) is the high word of e Fs: one multiply.  The row's
-  // largest value is that of ShiftExp(0) = I0 2^k_inter, which every row has;
-  // where it stays inside the output range no clamp is needed.  Otherwise the
-  // quotient is still below 2^k_out <= 2^8 (e F < 2^(32 + s_d) when
-  // S_sum >> s_d fits S_R; smaller when S_R is clamped), so the 16-bit
-  // clamp-and-pack holds it.
+  // floor(e F / 2^sh) is the high word of e Fs; from sh = 32 on it is the high
+  // word of e F shifted by the rest.  P_ANY: the quotient is below 2^k_out <=
+  // 2^8 whatever the parameters (e F < 2^(32 + s_d) when S_sum >> s_d fits S_R;
+  // smaller when S_R is clamped), so the 16-bit clamp-and-pack holds it.
   const uint32_t pcap = (1u << (a.k_out - 1)) - 1;
-  const uint32_t Fs = F << ((32 - sh) & 31);
-  const bool row_fast = FAST || (sh < 32 && F < (1u << (sh & 31)) &&
-                                 __umulhi((uint32_t)a.I0 << a.k_inter, Fs) <= pcap);
 
   // ---- phase 3: P and O = P V.  V is the A operand (rows = channels), P the
   // B operand (columns = query rows): a lane's bytes 4 u .. 4 u + 3 are the 4
@@ -387,13 +395,19 @@ void attention_kernel(AttnArgs a, uint32_t nrb, uint32_t ntiles) {
       if (j == (NBF - 1) / 2) vload_step(0);
     }
   };
-  if (FAST || __all(row_fast)) {
-    uint32_t Fr[NF];
+  if (P != P_ANY) {
+    const uint32_t Fs = F << (sh < 32 ? 32 - sh : 0);
+    uint32_t Fr[NF], tr[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) Fr[f] = __shfl(Fs, f * 16 + (lane & 15), 64);
+    for (int f = 0; f < NF; ++f) {
+      Fr[f] = __shfl(Fs, f * 16 + (lane & 15), 64);
+      tr[f] = P == P_SHIFT ? (uint32_t)__shfl(max(sh - 32, 0), f * 16 + (lane & 15), 64) : 0;
+    }
     pack_all([&](const int32_t(&e)[4], int f) {
-      return pack_bytes(__umulhi((uint32_t)e[0], Fr[f]), __umulhi((uint32_t)e[1], Fr[f]),
-                        __umulhi((uint32_t)e[2], Fr[f]), __umulhi((uint32_t)e[3], Fr[f]));
+      return pack_bytes(__umulhi((uint32_t)e[0], Fr[f]) >> tr[f],
+                        __umulhi((uint32_t)e[1], Fr[f]) >> tr[f],
+                        __umulhi((uint32_t)e[2], Fr[f]) >> tr[f],
+                        __umulhi((uint32_t)e[3], Fr[f]) >> tr[f]);
     });
   } else {
     const u16x2 pcap2 = {(unsigned short)pcap, (unsigned short)pcap};
@@ -517,46 +531,57 @@ __global__ __launch_bounds__(256) void qkv_relayout_kernel(const int8_t* qkv, Qk
   }
 }
 
-template <int R, int NW, int NB, bool FAST, bool HIGH = true>
+template <int R, int NW, int NB, PForm P, bool HIGH>
 hipError_t launch_variant(const AttnArgs& a, hipStream_t s) {
   const uint32_t nrb = (uint32_t)(a.Tw + R - 1) / R;
   const uint32_t ntiles = nrb * (uint32_t)(a.H * a.B * a.nW);
-  hipLaunchKernelGGL((attention_kernel<R, NW, NB, FAST, HIGH>), dim3(ntiles), dim3(64 * NW), 0, s,
-                     a, nrb, ntiles);
+  hipLaunchKernelGGL((attention_kernel<R, NW, NB, P, HIGH>), dim3(ntiles), dim3(64 * NW), 0, s, a,
+                     nrb, ntiles);
   return hipGetLastError();
 }
 
-// The instance with nb slots, LO <= nb <= HI.
+// The instance with nb slots, LO <= nb <= HI.  A wave holds 16 nb keys of a
+// row, a lane 4 nb, each of at most ShiftExp(0): their 32-bit sums are exact
+// while that many ShiftExp(0) stay below 2^32.
 template <int R, int NW, int LO, int HI>
-hipError_t launch_slots(const AttnArgs& a, int32_t nb, bool fast, hipStream_t s) {
+hipError_t launch_slots(const AttnArgs& a, int32_t nb, PForm p, hipStream_t s) {
   if constexpr (LO < HI) {
-    if (nb > LO) return launch_slots<R, NW, LO + 1, HI>(a, nb, fast, s);
+    if (nb > LO) return launch_slots<R, NW, LO + 1, HI>(a, nb, p, s);
   }
-  // 32-bit sums over a wave's keys are exact while 16 nb ShiftExp(0) < 2^32
-  if (!fast || ((int64_t)a.I0 << a.k_inter) * 16 * LO >= ((int64_t)1 << 32))
-    return launch_variant<R, NW, LO, false>(a, s);
-  return a.score_shift >= 32 ? launch_variant<R, NW, LO, true, true>(a, s)
-                             : launch_variant<R, NW, LO, true, false>(a, s);
+  const int64_t lane = ((int64_t)a.I0 << a.k_inter) * 4 * LO;
+  if (p == P_ANY || lane >= ((int64_t)1 << 32)) return launch_variant<R, NW, LO, P_ANY, true>(a, s);
+  const bool high = a.score_shift >= 32;
+  if (p == P_MUL && lane * 4 < ((int64_t)1 << 32))
+    return high ? launch_variant<R, NW, LO, P_MUL, true>(a, s)
+                : launch_variant<R, NW, LO, P_MUL, false>(a, s);
+  return high ? launch_variant<R, NW, LO, P_SHIFT, true>(a, s)
+              : launch_variant<R, NW, LO, P_SHIFT, false>(a, s);
 }
 
-// Whether P = floor(e F / 2^sh) is one high-word multiply for every row of n
-// keys, and inside the output range without a clamp.  With E = ShiftExp(0) the
-// sum S lies in [E, n E], sh = 32 - k_out + s_d, F = floor((2^31 - 1) / S_R).
-//  * s_d < k_out gives sh < 32.
-//  * S_R >= 2^(k_out - s_d) gives F < 2^(31 - k_out + s_d) = 2^(sh - 1).
+// The cheapest form of P = floor(e F / 2^sh) that holds for every row of n
+// keys (32-bit sums aside).  With E = ShiftExp(0) the sum S lies in [E, n E],
+// sh = 32 - k_out + s_d, F = floor((2^31 - 1) / S_R).  The one-multiply forms
+// need F < 2^sh where sh < 32, and P inside the output range without a clamp.
+//  * s_d < k_out gives sh < 32: no shift after the multiply.
 //  * Static s_d <= k_inter: E is a multiple of 2^s_d, so S_R >= E / 2^s_d (or
 //    S_R is 2^31 - 1) and E F < 2^31 2^s_d = 2^(sh + k_out - 1), the limit.
-//  * Dynamic s_d > 0 has S > 2^(31 - m_p) and S_R >= 2^(30 - m_p); with
-//    E <= 2^(30 - m_p) other keys make up half of S, and E F stays below the
-//    limit by nearly a factor of two.  s_d = 0 is the static case.
-bool p_fast(const AttnArgs& a, int64_t n) {
+//    S_R >= 2^(k_out - s_d) gives F < 2^(31 - k_out + s_d) = 2^(sh - 1).
+//  * Dynamic s_d > 0 has S > 2^(31 - m_p) and S_R >= 2^(30 - m_p), F <=
+//    2^(m_p + 1); with E <= 2^(30 - m_p) other keys make up half of S, and E F
+//    stays below the limit by nearly a factor of two.  s_d = 0 is the static
+//    case.
+PForm p_form(const AttnArgs& a, int64_t n) {
   const int64_t E = (int64_t)a.I0 << a.k_inter;
-  if (a.s_d >= 0)
-    return a.s_d < a.k_out && a.s_d <= a.k_inter && (E >> a.s_d) >= ((int64_t)1 << a.k_out);
+  if (a.s_d >= 0) {
+    if (a.s_d > a.k_inter || (a.s_d < a.k_out && (E >> a.s_d) < ((int64_t)1 << a.k_out)))
+      return P_ANY;
+    return a.s_d < a.k_out ? P_MUL : P_SHIFT;
+  }
+  if (E < ((int64_t)1 << a.k_out) || a.m_p + a.k_out > 30 || E > ((int64_t)1 << (30 - a.m_p)))
+    return P_ANY;
   // the largest s_d: bit length of n E - 1, + m_p - 31
   const int32_t bits = 64 - __builtin_clzll((unsigned long long)(n * E));
-  return bits + a.m_p - 31 < a.k_out && E >= ((int64_t)1 << a.k_out) &&
-         a.m_p + a.k_out <= 30 && E <= ((int64_t)1 << (30 - a.m_p));
+  return bits + a.m_p - 31 < a.k_out ? P_MUL : P_SHIFT;
 }
 
 // Accumulator clamp of a requantization by m / 2^s: beyond |acc| = L the
@@ -597,21 +622,21 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
   // floor(z / I0) = umulhi(z, ceil(2^32 / I0)) for z <= k_inter I0 <= 16 I0:
   // the excess z (I0 ceil(2^32 / I0) - 2^32) < 16 I0^2 <= 2^32
   b.inv_I0 = a.I0 == 1 ? 0 : (uint32_t)((((uint64_t)1 << 32) + a.I0 - 1) / (uint32_t)a.I0);
-  const bool fast = p_fast(a, a.Tw);
+  const PForm p = p_form(a, a.Tw);
   const int32_t nkb = (a.Tw + 15) >> 4;  // 16-key blocks
   const int64_t wg32 = (int64_t)((a.Tw + 31) / 32) * a.H * a.B * a.nW;
   if (nkb <= 32) {
     // up to 512 keys: 4 waves, in 16-row blocks where 32-row blocks would
     // give fewer than two workgroups per CU (2 waves of twice the slots: the
     // medium encoder 1% slower)
-    return wg32 < 512 ? launch_slots<16, 4, 1, 8>(b, (nkb + 3) / 4, fast, s)
-                      : launch_slots<32, 4, 1, 8>(b, (nkb + 3) / 4, fast, s);
+    return wg32 < 512 ? launch_slots<16, 4, 1, 8>(b, (nkb + 3) / 4, p, s)
+                      : launch_slots<32, 4, 1, 8>(b, (nkb + 3) / 4, p, s);
   }
   // Longer rows: 8 waves, two workgroups per CU, which fill each other's
   // barriers (16 waves, one workgroup: 53 against 40 us at 4 x 6 heads of
   // 1600 keys); grids of at most one workgroup per CU spread over 16 waves.
-  if (wg32 <= 256) return launch_slots<32, 16, 3, 8>(b, (nkb + 15) / 16, fast, s);
-  return launch_slots<32, 8, 5, 16>(b, (nkb + 7) / 8, fast, s);
+  if (wg32 <= 256) return launch_slots<32, 16, 3, 8>(b, (nkb + 15) / 16, p, s);
+  return launch_slots<32, 8, 5, 16>(b, (nkb + 7) / 8, p, s);
 }
 
 hipError_t launch_qkv_relayout(const int8_t* qkv, int32_t B, const QkvLayout& L,

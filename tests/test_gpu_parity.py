@@ -629,6 +629,45 @@ def _attention_smax_case(case, smax):
     assert_same(got, ref, "attention shiftmax params")
 
 
+# (I0, s_d, m_p, k_inter, k_out) on both sides of where the forms of P change:
+# output shifts from 32 on (a dynamic s_d of 8 needs S >= 2^35, reached by 1600
+# equal scores from I0 = 328 on; a static one), 32-bit sums of a wave's and of a
+# lane's keys, ShiftExp(0) above 2^(30 - m_p), s_d above k_inter, small
+# ShiftExp(0) >> s_d.
+P_FORMS = [(315, -1, 4, 16, 8), (316, -1, 4, 16, 8), (327, -1, 4, 16, 8), (328, -1, 4, 16, 8),
+           (700, -1, 4, 16, 8), (1024, -1, 4, 16, 8), (1025, -1, 4, 16, 8),
+           (1260, -1, 3, 16, 8), (1261, -1, 3, 16, 8), (16383, -1, 4, 16, 8),
+           (64, 7, 4, 16, 8), (64, 8, 4, 16, 8), (12, 12, 4, 16, 8), (64, 16, 4, 16, 8),
+           (64, 17, 4, 16, 8), (1260, 9, 4, 16, 8), (1261, 9, 4, 16, 8), (16383, 31, 4, 16, 8),
+           (300, 4, 4, 4, 8), (300, 5, 4, 4, 8), (40, 2, 4, 4, 8), (400, -1, 4, 16, 2),
+           (400, 3, 4, 16, 3), (64, -1, 27, 16, 3), (64, -1, 28, 16, 3)]
+
+
+@pytest.mark.parametrize("case", [(1, 40, 40, 0, 0), (6, 40, 40, 0, 0), (1, 20, 20, 0, 0),
+                                  (40, 20, 20, 0, 0)])
+@pytest.mark.parametrize("form", P_FORMS)
+def test_attention_p_forms(case, form):
+    """Rows of equal scores (the largest sums), of one standing out, and random
+    ones, on grids that take 16, 8 and 4 waves a workgroup."""
+    B, gh, gw, wh, ww = case
+    I0, s_d, m_p, k_inter, k_out = form
+    say(f"attention p forms I0={I0} s_d={s_d} m_p={m_p} k_inter={k_inter} k_out={k_out} B={B} "
+        f"grid={gh}x{gw}")
+    g = rng(I0 + s_d + gh)
+    T = gh * gw
+    one = g.integers(-127, 128, (T, 192)).astype(np.int8)
+    one[: T // 3, :64] = 0
+    one[T // 3: T // 2, :64] = 127
+    one[7, 64:128] = 127
+    p = {"score_mult": (1 << 29) + 4321, "score_shift": 38, "smax_I0": I0,
+         "smax_k_inter": k_inter, "smax_k_out": k_out, "smax_m_p": m_p, "smax_s_d": s_d,
+         "pv_mult": (1 << 29) + 99, "pv_shift": 28 + k_out}
+    ref = oracle.attention(one, gh, gw, wh, ww, 1, 64, p["score_mult"], 38, I0, p["pv_mult"],
+                           p["pv_shift"], k_inter=k_inter, k_out=k_out, m_p=m_p, s_d=s_d)
+    got = host(ilw.ilw_attention(dev(np.stack([one] * B)), gh, gw, wh, ww, 1, p))
+    assert_same(got, np.stack([ref] * B), "attention p forms")
+
+
 @pytest.mark.parametrize("case", [(1, 40, 40, 0, 0, 1), (2, 40, 40, 20, 20, 1),
                                   (1, 6, 10, 3, 5, 1)])
 def test_attention_large_m_p(case):

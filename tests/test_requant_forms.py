@@ -248,3 +248,51 @@ def test_score_fast_condition_is_needed():
     assert rq_exact(1 << 20, 1 << 30, 12) == 127
     with pytest.raises(AssertionError, match="overflow"):
         rq_score_fast(1 << 20, (1 << 31) - 1, 64)
+
+
+# ------------------------------------------------------ probabilities by one multiply
+def p_form(I0, k_inter, k_out, m_p, s_d, n):
+    """The attention host's rule for rows of n keys: 0 one multiply, 1 that and
+    a shift, 2 the general form."""
+    E = I0 << k_inter
+    if s_d >= 0:
+        if s_d > k_inter or (s_d < k_out and (E >> s_d) < 1 << k_out):
+            return 2
+        return 0 if s_d < k_out else 1
+    if E < 1 << k_out or m_p + k_out > 30 or E > 1 << (30 - m_p):
+        return 2
+    return 0 if (n * E).bit_length() + m_p - 31 < k_out else 1
+
+
+def test_one_multiply_probabilities_are_exact():
+    """Every exponential of rows whose sum lies anywhere in [E, n E], E =
+    ShiftExp(0), by the host's form against min(floor(e F / 2^sh), cap)."""
+    rng = np.random.default_rng(12)
+    seen = [0, 0, 0]
+    for _ in range(6000):
+        I0 = int(rng.integers(1, 1 << int(rng.integers(1, 15))))
+        k_inter, k_out = int(rng.choice([16, 16, 4, int(rng.integers(1, 17))])), \
+            int(rng.choice([8, 8, int(rng.integers(2, 9))]))
+        m_p = int(rng.choice([4, 4, int(rng.integers(0, 32))]))
+        s_d = int(rng.choice([-1, -1, int(rng.integers(0, 32))]))
+        n, E = int(rng.integers(1, 2049)), I0 << k_inter
+        form = p_form(I0, k_inter, k_out, m_p, s_d, n)
+        seen[form] += 1
+        if form == 2:
+            continue
+        cap = (1 << (k_out - 1)) - 1
+        sums = {E, n * E, *(int(E * (n ** v)) for v in rng.random(6))}
+        for p2 in (31, 32, 35 - m_p, (E * n).bit_length() - 1):
+            sums.update(v for v in ((1 << max(p2, 0)) - 1, 1 << max(p2, 0)) if E <= v <= n * E)
+        for S in sums:
+            sd = s_d if s_d >= 0 else max(0, (S - 1).bit_length() + m_p - 31)
+            F = ((1 << 31) - 1) // max(1, min(S >> sd, (1 << 31) - 1))
+            sh = min(32 - k_out + sd, 63)
+            assert sh >= 32 or F < 1 << sh
+            Fs = F << (32 - sh) if sh < 32 else F
+            assert Fs < 1 << 32 and (form == 1 or sh < 32)
+            # the largest value, one that may be the row's only other one, and any
+            for e in {E, E >> 1, S - E if S - E < E else 0, int(rng.integers(0, E + 1))}:
+                got = ((e * Fs) >> 32) >> max(sh - 32, 0)
+                assert got == min((e * F) >> sh, cap), (I0, k_inter, k_out, m_p, s_d, S, e)
+    assert min(seen) > 300, seen
