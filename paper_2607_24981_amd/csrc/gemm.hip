@@ -448,7 +448,12 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
   };
   const bool gen = unbounded != 0 || (RES && a.res_shift < 9);
   if (gen) {
-    requant_tile(Flag<true>{}, Flag<false>{});
+    if constexpr (BRANCH_FREE) {
+      if (full_tile) requant_tile(Flag<true>{}, Flag<true>{});
+      else requant_tile(Flag<true>{}, Flag<false>{});
+    } else {
+      requant_tile(Flag<true>{}, Flag<false>{});
+    }
   } else {
     if constexpr (BRANCH_FREE) {
       if (full_tile) requant_tile(Flag<false>{}, Flag<true>{});

@@ -123,6 +123,30 @@ def test_linear_requant_forms(M, fallback):
     assert_same(got, ref, "linear requant forms")
 
 
+@pytest.mark.parametrize("shifts", [(15, 20), (39, 42)])
+@pytest.mark.parametrize("M,N,K", [(16448, 256, 192), (24577, 256, 192), (32640, 256, 64),
+                                   (17409, 320, 192), (9408, 448, 80), (21889, 192, 256),
+                                   (27201, 192, 272), (16385, 256, 320)])
+def test_linear_tile_rules(M, N, K, shifts):
+    """Both tiles of grids of fewer than two 128 x 128 tiles per CU (wide and
+    narrow, short and longer sums, whole and partial tiles), with channels that
+    need the accumulator clamp (multipliers near 2^30 over shifts of 15 to 19)
+    and without: every 53rd row and both ends against the oracle."""
+    say(f"linear tile rules M={M} N={N} K={K} shifts={shifts}")
+    g = rng(M + N + K + shifts[0])
+    x = np.clip(np.round(g.normal(0, 42, (M, K))), -127, 127).astype(np.int8)
+    x[::7] = 0  # sums that are the bias alone: not all saturated by small shifts
+    w = g.integers(-127, 128, (N, K)).astype(np.int8)
+    b = g.integers(-2 ** 15, 2 ** 15, N).astype(np.int32)
+    if shifts[0] < 20:
+        b[::2] = 0
+    mult = g.integers(2 ** 29, 2 ** 30, N).astype(np.int32)
+    shift = g.integers(*shifts, N).astype(np.int32)
+    rows = np.unique(np.r_[0:130, 0:M:53, M - 130:M])
+    got = host(ilw.ilw_linear(dev(x), dev(w), dev(b), dev(mult), dev(shift)))
+    assert_same(got[rows], oracle.linear(x[rows], w, b, mult, shift), "linear tile rules")
+
+
 def test_linear_no_bias_and_empty():
     say("linear without bias, M=0")
     g = rng(5)
