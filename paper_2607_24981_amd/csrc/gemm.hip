@@ -752,10 +752,22 @@ hipError_t launch_gemm(int epi, const GemmArgs& a_in, hipStream_t s) {
   // on each of two streams, 15-20% faster than the one-wave tiles below)
   if (epi == EPI_QKV && a.N >= 1024) return launch_tile<4, 2, 4, 4, 1>(epi, a, s);
   // Fewer 128 x 128 tiles than two per CU: 128-channel x 64-token tiles of 4
-  // waves with two K steps of loads in flight (the patch embedding of 8 640x640
-  // frames 17.1 -> 15.0 us against one-wave 64 x 64 tiles with one).
+  // waves with two K steps of loads in flight, or one-wave 64 x 64 tiles (the
+  // patch embedding of 8 640x640 frames 15.0 and 17.1 us).  With four K steps
+  // or more the wide tiles win unless the CU with the most work then has over
+  // 1.5 times that of the narrow ones (25 600 tokens of 768 to 192: 18.4 us
+  // wide, 17.1 narrow; 21 888 tokens 11.5 and 13.0).  Shorter sums are mostly
+  // epilogue: wide tiles without idle channels, up to three per CU (16 448
+  // tokens of 192 to 256 6.3 us wide, 6.6 narrow; 32 640 tokens 8.2 and 7.9;
+  // 21 760 tokens of 192 to 320 8.7 and 7.9).
   const int64_t big_tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (big_tiles < 512) return launch_tile<2, 2, 4, 2, 2, TK, false>(epi, a, s);
+  if (big_tiles < 512) {
+    const int64_t narrow = mt64 * ((a.N + 63) / 64), wide = mt64 * ((a.N + 127) / 128);
+    const bool take_wide = a.K >= 4 * TK ? 4 * ((wide + 255) / 256) <= 3 * ((narrow + 255) / 256)
+                                         : narrow == 2 * wide && wide <= 3 * 256;
+    return take_wide ? launch_tile<2, 2, 4, 2, 2, TK, false>(epi, a, s)
+                     : launch_tile<1, 1, 4, 4, 1>(epi, a, s);
+  }
   if (a.N % 192 == 0 && a.K >= 768) return launch_tile<3, 2, 4, 4, 1>(epi, a, s);
   if (a.N == 192) return launch_tile<3, 1, 4, 4, 1>(epi, a, s);
   return launch_tile<2, 4, 4, 2, 1>(epi, a, s);
