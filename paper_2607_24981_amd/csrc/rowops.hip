@@ -290,7 +290,7 @@ __global__ __launch_bounds__(256) void shiftmax_kernel(const int8_t* x, int8_t* 
 // odd bytes.
 // Bound by the memory round trip at a few thousand rows: 19 200 rows of 300
 // scores 13.3 -> 6.2 us against one wave per row with byte accesses.
-template <int LPR, int JC>
+template <int LPR, int JC, bool RAGGED>
 __global__ __launch_bounds__(256) void shiftmax_rows_kernel(const int8_t* x, int8_t* y,
                                                             int64_t rows, int32_t cols,
                                                             int32_t I0, int32_t k_inter,
@@ -300,16 +300,18 @@ __global__ __launch_bounds__(256) void shiftmax_rows_kernel(const int8_t* x, int
   constexpr int RG = 64 / LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / LPR, k = lane % LPR;
-  const int32_t n16 = (cols + 15) >> 4, ov = n16 * 16 - cols;
+  const int32_t n16 = (cols + 15) >> 4, ov = RAGGED ? n16 * 16 - cols : 0;
   const int64_t ngroups = (rows + RG - 1) / RG;
   const int64_t gstride = (int64_t)gridDim.x * 4;
   // chunks past the row repeat its last 16 values: they cannot raise the max
+  auto chunk_at = [&](int32_t ch) {
+    return RAGGED ? min(ch * 16, cols - 16) : min(ch, n16 - 1) * 16;
+  };
   auto load = [&](int64_t g, v4i(&v)[JC]) {
     const int64_t row = min(g * RG + sub, rows - 1);
     const int8_t* xr = x + row * cols;
 #pragma unroll
-    for (int j = 0; j < JC; ++j)
-      v[j] = *(const v4i_any*)(xr + min((k + j * LPR) * 16, cols - 16));
+    for (int j = 0; j < JC; ++j) v[j] = *(const v4i_any*)(xr + chunk_at(k + j * LPR));
   };
   int64_t g = (int64_t)blockIdx.x * 4 + wave;
   v4i nxt[JC];
@@ -353,7 +355,7 @@ __global__ __launch_bounds__(256) void shiftmax_rows_kernel(const int8_t* x, int
         }
         sum += ws;  // 4 values of at most 2^30 each
       }
-      if (ov > 0 && k + j * LPR == n16 - 1) {
+      if (RAGGED && k + j * LPR == n16 - 1) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(256) void shiftmax_rows_kernel(const int8_t* x, int
                        : (uint32_t)min(((uint64_t)e[j][q][b] * F) >> sh, (uint64_t)cap);
           o[q] = (int32_t)pack_min_bytes(p[0], p[1], p[2], p[3], cap2);
         }
-        if (live) *(v4i_any*)(yr + min(ch * 16, cols - 16)) = o;
+        if (live) *(v4i_any*)(yr + (RAGGED ? chunk_at(ch) : ch * 16)) = o;
       }
     };
     if (__all(sh < 32 && F < (1u << (sh & 31))))
@@ -607,22 +609,38 @@ hipError_t launch_shiftmax(const int8_t* x, int8_t* y, int64_t rows, int32_t col
       const int64_t groups = (rows + (64 / LPR) - 1) / (64 / LPR);
       int64_t wgs = (groups + 3) / 4;
       if (wgs > 4096) wgs = 4096;
-      hipLaunchKernelGGL((shiftmax_rows_kernel<LPR, JC>), dim3((unsigned)wgs), dim3(256), 0, s,
-                         x, y, rows, cols, I0, k_inter, k_out, m_p, s_d);
+      auto launch = [&](auto ragged) {
+        hipLaunchKernelGGL((shiftmax_rows_kernel<LPR, JC, decltype(ragged)::value>),
+                           dim3((unsigned)wgs), dim3(256), 0, s, x, y, rows, cols, I0, k_inter, k_out,
+                           m_p, s_d);
+      };
+      if (cols % 16)
+        launch(Flag<true>{});
+      else
+        launch(Flag<false>{});
       return hipGetLastError();
     };
-    // the split with the fewest idle chunks (at least three quarters of them
-    // are in use past 64 values)
+    // As few chunks a lane as leave the launch at most 8 waves per CU: up to
+    // there its time is one wave's chain, past it the instructions of all (4096
+    // rows of 320: 3.5, 3.5 and 3.8 us with 1, 2 and 3 chunks, 16 384 rows 6.5,
+    // 5.4 and 5.0).  Three only where two lanes' worth would leave more idle
+    // (at least 5 of 8 chunks are in use everywhere).
+    auto fits = [&](int64_t lanes) { return rows * lanes <= 64 * 8 * 256; };
     if (n16 <= 4) return go(IntC<4>{}, IntC<1>{});
     if (n16 <= 8) return go(IntC<8>{}, IntC<1>{});
-    if (n16 <= 12) return go(IntC<4>{}, IntC<3>{});
-    if (n16 <= 16) return go(IntC<8>{}, IntC<2>{});
-    if (n16 <= 24) return go(IntC<8>{}, IntC<3>{});
-    if (n16 <= 32) return go(IntC<16>{}, IntC<2>{});
-    if (n16 <= 48) return go(IntC<16>{}, IntC<3>{});
-    if (n16 <= 64) return go(IntC<32>{}, IntC<2>{});
-    if (n16 <= 96) return go(IntC<32>{}, IntC<3>{});
-    return go(IntC<64>{}, IntC<2>{});
+    if (n16 <= 16) {
+      if (fits(16)) return go(IntC<16>{}, IntC<1>{});
+      return fits(8) || n16 > 12 ? go(IntC<8>{}, IntC<2>{}) : go(IntC<4>{}, IntC<3>{});
+    }
+    if (n16 <= 32) {
+      if (fits(32)) return go(IntC<32>{}, IntC<1>{});
+      return fits(16) || n16 > 24 ? go(IntC<16>{}, IntC<2>{}) : go(IntC<8>{}, IntC<3>{});
+    }
+    if (n16 <= 64) {
+      if (fits(64)) return go(IntC<64>{}, IntC<1>{});
+      return fits(32) || n16 > 48 ? go(IntC<32>{}, IntC<2>{}) : go(IntC<16>{}, IntC<3>{});
+    }
+    return fits(64) || n16 > 96 ? go(IntC<64>{}, IntC<2>{}) : go(IntC<32>{}, IntC<3>{});
   }
   dim3 grid((unsigned)((rows + 3) / 4)), block(256);
   hipLaunchKernelGGL(shiftmax_kernel, grid, block, 0, s, x, y, rows, cols, I0, k_inter,

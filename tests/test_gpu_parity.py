@@ -240,7 +240,6 @@ def test_shiftmax_row_chunks(rows, cols, s_d):
     assert_same(host(t), oracle.shiftmax_rows(x, 30, s_d=s_d), "shiftmax row chunks in place")
 
 
-# ------------------------------------------------------------------ SD-ShiftGELU
 @pytest.mark.parametrize("cols", [15, 16, 17, 49, 64, 65, 129, 193, 257, 300, 385, 513, 769, 1025,
                                   1537, 2047, 2048, 2049])
 @pytest.mark.parametrize("offset", [0, 3])
@@ -263,6 +262,20 @@ def test_shiftmax_ragged_rows(cols, offset):
     assert int(buf[:offset].abs().sum()) == 0 and int(buf[offset + rows * cols:].abs().sum()) == 0
 
 
+@pytest.mark.parametrize("rows,cols", [(r + d, c) for r, c in
+                                       [(8192, 144), (8192, 250), (16384, 192), (4096, 272),
+                                        (4096, 300), (4096, 500), (8192, 384), (2048, 528),
+                                        (2048, 999), (4096, 700), (2048, 1040), (2048, 1500)]
+                                       for d in (0, 1)])
+def test_shiftmax_row_counts(rows, cols):
+    """Row counts on both sides of where a row is split over fewer lanes."""
+    say(f"shiftmax row counts {rows}x{cols}")
+    x = rng(rows + cols).integers(-128, 128, (rows, cols)).astype(np.int8)
+    assert_same(host(ilw.ilw_shiftmax(dev(x), 12)), oracle.shiftmax_rows(x, 12, s_d=-1),
+                "shiftmax row counts")
+
+
+# ------------------------------------------------------------------ SD-ShiftGELU
 @pytest.mark.parametrize("I0", [1, 8, 16, 37, 64, 1000, 16383])
 def test_sdshiftgelu_exhaustive(I0):
     say(f"sdshiftgelu exhaustive I0={I0}")
