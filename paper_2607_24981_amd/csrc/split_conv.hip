@@ -185,7 +185,8 @@ __global__ __launch_bounds__(64 * WN * WM) void split_conv_kernel(SplitArgs a, i
       bound += (((int64_t)a.C[b] << 14) * (m < 0 ? -m : m) >> a.bshift[b][q]) + 1;
     }
     const int32_t bias = a.bias ? a.bias[n] : 0;
-    wide |= bound > INT32_MAX || bound + llabs((int64_t)bias) >= ((int64_t)3 << 30);
+    const int64_t ab = bias < 0 ? -(int64_t)bias : bias;
+    wide |= (bound > INT32_MAX) | (bound + ab >= (int64_t)3 << 30);
     const int32_t q = a.onq == 1 ? 0 : n;
     RqI64 r;
     r.init(a.omult[q], a.oshift[q], bias);
