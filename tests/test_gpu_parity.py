@@ -955,10 +955,20 @@ def test_encoder_mid_batches(name, batch):
                                           (328, 1536)])
 def test_block_tail_token_groups(batch, hidden):
     """The 384-wide block tail on 16 and 64 tokens a workgroup, at ragged token
-    counts on both sides of the change (4075, 4100, 8175, 8200 tokens)
-    and the smallest, with and without the next block's LayerNorm: the first,
-    a middle and the last image against the oracle."""
-    D, H, gh, gw = 384, 6, 5, 5
+    counts on both sides of the change at 4096 (4075 and 4100 tokens), far past
+    it (8175 and 8200) and the smallest, with and without the next block's
+    LayerNorm: the first, a middle and the last image against the oracle."""
+    _block_tail_case(batch, hidden, 5)
+
+
+@pytest.mark.parametrize("batch", [255, 256, 257])
+def test_block_tail_token_limit(batch):
+    """The same with 4080, 4096 and 4112 tokens."""
+    _block_tail_case(batch, 384, 4)
+
+
+def _block_tail_case(batch, hidden, side):
+    D, H, gh, gw = 384, 6, side, side
     say(f"block tail token groups batch={batch} hidden={hidden}")
     blocks = [synth.block_params(rng(90 + i), D, H, 64, hidden, "wide") for i in range(2)]
     x = np.clip(np.round(rng(93).normal(0, 42, (batch, gh * gw, D))), -127, 127).astype(np.int8)
@@ -1511,7 +1521,8 @@ def test_split_conv_projector_b1_full(per_channel):
 
 
 def test_split_conv_projector_b32_sampled():
-    """Batch 32 (the large-tile launch): three images against the oracle."""
+    """Batch 32 (64 x 64 tiles on a large grid: four of them read a token):
+    three images against the oracle."""
     wl = synth.SPLIT_WORKLOADS["splitconv_t1600_c3x192_n256_b32"]
     say(wl.name)
     d = synth.split_conv_inputs(wl, 6)
@@ -1523,6 +1534,25 @@ def test_split_conv_projector_b32_sampled():
         ref = oracle.split_conv([x[rows] for x in d["xs"]], d["ws"], d["branch_mults"],
                                 d["branch_shifts"], d["bias"], d["out_mult"], d["out_shift"])
         assert_same(got[rows], ref, f"image {b}")
+
+
+@pytest.mark.parametrize("per_channel", [False, True])
+@pytest.mark.parametrize("M,N", [(11001, 400), (12800, 320)])
+def test_split_conv_large_tiles(M, N, per_channel):
+    """128 x 64 tiles (more than 256 outputs, over 4096 waves of 32 x 32), with
+    and without a partial last tile either way, some of whose channels have sums
+    or biases beyond the int32 epilogue: every 41st row and both ends."""
+    say(f"split conv large tiles M={M} N={N} per_channel={per_channel}")
+    g = rng(M + N + per_channel)
+    xs, ws, bm, bs, bias, om, os_ = _split_case(g, M, N, (64, 192, 128), per_channel)
+    bias[130] = (1 << 31) - 1
+    bias[N - 1] = -(1 << 31)
+    if per_channel:
+        bm[1][70], bs[1][70] = (1 << 31) - 1, 9
+        om[70], os_[70] = 3, 38
+    rows = np.unique(np.r_[0:129, 0:M:41, M - 129:M])
+    ref = oracle.split_conv([x[rows] for x in xs], ws, bm, bs, bias, om, os_)
+    assert_same(_split_gpu(xs, ws, bm, bs, bias, om, os_)[rows], ref, "split conv large tiles")
 
 
 # ------------------------------------------------------------------ deformable sampling
