@@ -368,12 +368,12 @@ hipError_t launch_deform(const DeformArgs& a, hipStream_t s) {
   const int64_t groups = (int64_t)a.B * a.Q * a.H;
   if (groups == 0) return hipSuccess;
   const int32_t words = a.Dh / 4, G = group_lanes(words), LP = a.L * a.P, J = (LP + G - 1) / G;
-  // The group kernel up to 4 samples a lane, where its threads and an image's
-  // word offsets are 32-bit.  It is the faster one also with idle lanes: 48
+  // The group kernel up to 4 samples a lane, where a launch holds its threads (in
+  // whole workgroups below 2^32) and an image's word offsets are 32-bit.  It is the faster one also with idle lanes: 48
   // channels per head on 16 lanes, 8 x 300 queries, 8 heads, 12 samples:
   // nearest 7.6 us (the general kernel 25.8), boxes and bilinear 13.1
   // (44.3).
-  if (J <= 4 && groups * G <= UINT32_MAX && (int64_t)a.S * a.H * words <= UINT32_MAX) {
+  if (J <= 4 && groups * G <= (int64_t)UINT32_MAX - 255 && (int64_t)a.S * a.H * words <= UINT32_MAX) {
     const dim3 grid((unsigned)((groups * G + 255) / 256));
     return a.mode == 0 ? launch_group<0>(a, J, grid, s) : launch_group<1>(a, J, grid, s);
   }

@@ -1556,6 +1556,26 @@ def test_split_conv_large_tiles(M, N, per_channel):
 
 
 # ------------------------------------------------------------------ deformable sampling
+def test_deform_largest_group_launch():
+    """Twelve words a head on 16 lanes with 2^28 - 8 groups: whole workgroups of
+    the group kernel would be 2^32 threads, one more than a launch holds, so the
+    general kernel (12 lanes a group) runs it."""
+    Q, H, Dh = (1 << 25) - 1, 8, 48
+    say(f"deform Q={Q} heads={H} head_dim={Dh}")
+    value = rng(5).integers(-127, 128, (1, 4, H, Dh)).astype(np.int8)
+    hw, start = np.array([[2, 2]], np.int32), np.zeros(1, np.int32)
+    ref = torch.full((1, Q, 2), 40000, dtype=torch.int32, device="cuda")
+    off = torch.zeros((1, Q, H, 1, 1, 2), dtype=torch.int16, device="cuda")
+    lg = torch.zeros((1, Q, H, 1), dtype=torch.int8, device="cuda")
+    want = oracle.deform_attn(value, hw, start, host(ref[:, :1]), host(off[:, :1]),
+                              host(lg[:, :1]), 16, 1 << 30, 36)
+    assert np.unique(want).size > 50
+    got = ilw.ilw_deform_attn(dev(value), hw, start, ref, off, lg, 16, 1 << 30, 36)[0]
+    w = dev(want).view(1, H * Dh)
+    for q in range(0, Q, 1 << 22):
+        assert bool((got[q:q + (1 << 22)] == w).all()), f"queries from {q}"
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 def test_deform_c5_full(mode):
     wl = synth.DEFORM_WORKLOADS["deform_q300_d256_b8"]
