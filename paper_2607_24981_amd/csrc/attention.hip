@@ -641,7 +641,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s) {
 
 hipError_t launch_qkv_relayout(const int8_t* qkv, int32_t B, const QkvLayout& L,
                                hipStream_t s) {
-  // batch * tokens < 2^23 and dim <= 16384 keep the counts below 2^32
+  // a launch holds fewer than 2^32 threads (over 68 GB of Q | K | V reach that)
   const int64_t n_qk = (int64_t)B * L.T * (2 * L.D / 16);
   const int64_t n_v = (int64_t)B * L.nW * ((L.Tw + 3) / 4) * (L.D / 16);
   if (n_qk == 0) return hipSuccess;

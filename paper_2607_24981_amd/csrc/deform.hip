@@ -3,11 +3,12 @@
 // bilinear blend; Sec. 3.3.2: the sampling weights are Constrained Shiftmax
 // of the L*P logits of each (image, query, head)).
 //
-// A group of head_dim/4 lanes serves one (image, query, head); each lane owns
-// four channels, so the head slice of one sample (head_dim bytes) is read by
-// the group as consecutive 32-bit words.  The L*P weights are recomputed by
-// every lane of the group from a per-workgroup ShiftExp table: it costs a few
-// table reads and saves a cross-lane exchange.
+// A group of lanes serves one (image, query, head); a lane owns four channels,
+// so the head slice of one sample (head_dim bytes) is read by the group as
+// consecutive 32-bit words.  The group kernel divides the L*P samples among its
+// lanes, which exchange their words and weights through LDS; the general
+// kernel, for what that one does not hold (launch_deform), has head_dim/4 lanes
+// a group and makes every weight in every lane.
 //
 // Sampling locations are Q8 pixels of each level.  A reference point (x, y)
 // lands at floor(x W / 2^8) and the offset adds Q8 pixels.  A reference box
@@ -368,12 +369,13 @@ hipError_t launch_deform(const DeformArgs& a, hipStream_t s) {
   const int64_t groups = (int64_t)a.B * a.Q * a.H;
   if (groups == 0) return hipSuccess;
   const int32_t words = a.Dh / 4, G = group_lanes(words), LP = a.L * a.P, J = (LP + G - 1) / G;
-  // The group kernel up to 4 samples a lane, where a launch holds its threads (in
-  // whole workgroups below 2^32) and an image's word offsets are 32-bit.  It is the faster one also with idle lanes: 48
-  // channels per head on 16 lanes, 8 x 300 queries, 8 heads, 12 samples:
-  // nearest 7.6 us (the general kernel 25.8), boxes and bilinear 13.1
-  // (44.3).
-  if (J <= 4 && groups * G <= (int64_t)UINT32_MAX - 255 && (int64_t)a.S * a.H * words <= UINT32_MAX) {
+  // The group kernel up to 4 samples a lane, where a launch holds its threads
+  // (fewer than 2^32 in whole workgroups) and an image's word offsets are
+  // 32-bit.  It is the faster one also with idle lanes: 48 channels per head on
+  // 16 lanes, 8 x 300 queries, 8 heads, 12 samples: nearest 7.6 us (the general
+  // kernel 25.8), boxes and bilinear 13.1 (44.3).
+  if (J <= 4 && groups * G <= (int64_t)UINT32_MAX - 255 &&
+      (int64_t)a.S * a.H * words <= UINT32_MAX) {
     const dim3 grid((unsigned)((groups * G + 255) / 256));
     return a.mode == 0 ? launch_group<0>(a, J, grid, s) : launch_group<1>(a, J, grid, s);
   }

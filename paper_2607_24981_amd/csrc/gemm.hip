@@ -377,11 +377,11 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
     }
   }
   // The residual add has a 32-bit form for shifts >= 9 (uniform per launch),
-  // the accumulators of a tile whose channels are all bounded need no clamp
-  // (`general` covers the other cases of both), and tiles inside M x N need no per-lane validity tests (whose exec-mask
-  // branches would split the loop into blocks the compiler cannot
-  // interleave): the loop below is instantiated for each case and selected
-  // once per workgroup.
+  // and the accumulators of a tile whose channels are all bounded need no clamp
+  // (`general` covers the other cases of both).  Tiles inside M x N need no
+  // per-lane validity tests, whose exec-mask branches would split the loop into
+  // blocks the compiler cannot interleave.  The loop below is instantiated for
+  // each case and selected once per workgroup.
   const bool full_tile = BRANCH_FREE && n0 + TN <= N && m0 + TM <= M;
   // (with quads M is a multiple of 4: a quad of tokens is valid as a whole)
   const bool v_quads = EPI == EPI_QKV && vt_quads(a.qkv);

@@ -395,9 +395,10 @@ enum GemmEpilogue {
 // Window-major Q, K [B, nW, H, Tw, 64] and V [B, nW, H, Twp / 16, 4, 4, 16, 4]
 // (Twp = Tw rounded to 64): Q and K rows of 64 bytes per head; V in blocks of
 // 16 keys as [channel / 16][key / 4][channel % 16][key % 4], so that an
-// attention wave's load of 4 keys per lane is 256 consecutive bytes.  64 channels per head whatever the head dimension (2^hs,
-// 32 or 64); the bytes past the head dimension are never written and never
-// used, and those of keys past the window carry no weight.
+// attention wave's load of 4 keys per lane is 256 consecutive bytes.  64
+// channels per head whatever the head dimension (2^hs, 32 or 64); the bytes past
+// the head dimension are never written and never used, and those of keys past
+// the window carry no weight.
 struct QkvLayout {
   int8_t* q;
   int8_t* k;

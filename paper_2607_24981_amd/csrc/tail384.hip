@@ -487,11 +487,14 @@ hipError_t launch_tail384(const GemmArgs& fp, const GemmArgs& f1, const GemmArgs
       f2.K != f1.N || f2.N != T_D || !fp.wp || !f1.wp || !f2.wp)
     return hipErrorInvalidValue;
   // 16 tokens per workgroup while that keeps the grid within one workgroup
-  // per CU, else 64.  (32 are faster up to 8192 tokens alone, but fill the
-  // CUs that half batches on two streams share.)  Up to there a launch takes as long as one workgroup, whose time
-  // is its epilogues' VALU work (proportional to its tokens) above the weight
-  // stream (1.3 MB through one CU whatever its tokens: 8.6 us at 64 bytes a
-  // cycle); past it the smaller tiles only read the weights more often.
+  // per CU, else 64.  Up to there a launch takes as long as one workgroup, whose
+  // time is its epilogues' VALU work (proportional to its tokens) above the
+  // weight stream (1.3 MB through one CU whatever its tokens: 8.6 us at 64 bytes
+  // a cycle); past it the smaller tiles only read the weights more often.  From
+  // 4097 to 8192 tokens 32 a workgroup are faster on one stream (ten blocks of
+  // 6400 tokens 625 -> 559 us) and slower where two streams' halves of a batch
+  // share the CUs (two of 6400 861 -> 898 us, two of 8000 990 -> 1063), which
+  // is how such batches are meant to run.
   // Whole blocks (mlp 1536, us) with 16 / 32 / 64 tokens a workgroup:
   //   256 tokens 36.7 / 39.7 / 44.6    2048 tokens 39.9 / 42.0 / 48.0
   //   4096       43.4 / 45.0 / 51.4    7168        65.4 / 53.1 / 58.6
