@@ -43,6 +43,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 def short(name: str) -> str:
     name = name.replace("ilw::(anonymous namespace)::", "").replace("void ", "")
+    name = re.sub(r"\((?:\w+::)*\w+\)(?=\d)", "", name)  # the type of an enum argument
     return re.sub(r"\(.*$", "", name)
 
 
