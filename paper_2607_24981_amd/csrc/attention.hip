@@ -22,12 +22,13 @@
 //
 // Bound: VALU instructions.  gfx950 issues the 64-bit multiply-add, the
 // permutes and the medians at one rate, 4 cycles per wave, so their number is
-// what counts: about 10.5 per 64 scores (7 of them requantize, address the
-// table, sum, multiply and pack) against 12 with score rows in LDS; the two
-// matmuls take a tenth of the time beside them.  Measured against 32-row
-// blocks whose scores and probabilities went through LDS, on 1600-key rows
-// (2400 workgroups) 64.4 -> 59.0 us, 1200 workgroups 36.7 -> 30.5 us, 400-key
-// windows (4992 workgroups) 40.8 -> 34.8 us.
+// what counts: by the counters 12.1 per 64 scores of 1600-key rows (7 of them
+// requantize, address the table, sum, multiply and pack) at 60 to 70% VALU
+// busy, 14.7 on 400-key windows, where score rows in LDS took 11.9 at 55 to 65%
+// and 19.8; the two matmuls take an eighth of the time beside them.  Against
+// 32-row blocks whose scores and probabilities went through LDS, on 1600-key
+// rows (2400 workgroups) 64.4 -> 59.0 us, 1200 workgroups 36.7 -> 30.5 us,
+// 400-key windows (4992 workgroups) 40.8 -> 34.8 us.
 #include "ilw_internal.h"
 
 namespace ilw {
