@@ -47,7 +47,8 @@ constexpr int kRow = kCopies * 4;  // bytes per table entry
 // Slots of 16 keys whose exponentials a wave keeps in registers, of nb; the
 // scores of the others are kept as bytes and looked up twice (for the sum, and
 // again for P), which keeps the kernel within the 128 registers of four waves
-// per SIMD (16 more slots' worth would be spilled).
+// per SIMD up to 13 slots.  14 to 16 (rows past 1664 keys) still spill 2 to 24
+// registers in the score phase, with fewer slots kept as well.
 constexpr int full_slots(int nb) { return nb <= 10 ? nb : nb <= 12 ? 10 : nb <= 14 ? 9 : 8; }
 
 // The scores are kept complemented, n = ~q = -q - 1 in [-128, 126]: the row
