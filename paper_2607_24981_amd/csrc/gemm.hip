@@ -142,15 +142,16 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
   constexpr int PW = (CW + NT - 1) / NT, PX = (CX + NT - 1) / NT;
   const int8_t* wsrc[PW];
   const int8_t* xsrc[PX];
-  int kofs[PW > PX ? PW : PX];
+  const int kofs = (tid % CPR) * 16;  // the same chunk of every row a thread loads
+  static_assert(NT % CPR == 0, "kofs holds for every i");
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int c = min(tid + i * NT, CW - 1);
+    const int c = min(tid + i * NT, CW - CPR + tid % CPR);
     wsrc[i] = W + (int64_t)min(n0 + c / CPR, N - 1) * K + (c % CPR) * 16;
   }
 #pragma unroll
   for (int i = 0; i < PX; ++i) {
-    const int c = min(tid + i * NT, CX - 1);
+    const int c = min(tid + i * NT, CX - CPR + tid % CPR);
     const int64_t m = min(m0 + c / CPR, M - 1);
     if (XP) {
       // top-left pixel of the token's patch; K offsets are added per step
@@ -162,8 +163,6 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
       xsrc[i] = X + m * K + (c % CPR) * 16;
     }
   }
-#pragma unroll
-  for (int i = 0; i < (PW > PX ? PW : PX); ++i) kofs[i] = ((tid + i * NT) % CPR) * 16;
   // The loads of K step k go to register slot k % PF.
   v4i rw[PF][PW], rx[PF][PX];
   const int nk = (K + KB - 1) / KB;
@@ -172,8 +171,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
       if (KTAIL) {
-        const bool ok = kb + kofs[i] < K;
-        rw[sl][i] = *(const v4i*)(wsrc[i] + (ok ? kb : 0));
+        const bool ok = kb + kofs < K;  // past K: the row's first chunk, never used
+        rw[sl][i] = *(const v4i*)(wsrc[i] + (ok ? kb : -kofs));
         if (!ok) rw[sl][i] = zero;
       } else {
         rw[sl][i] = *(const v4i*)(wsrc[i] + kb);
@@ -183,12 +182,12 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
     for (int i = 0; i < PX; ++i) {
       if (XP) {
         // the chunk's 16 K values are pixels kx = 0..15 of row ky of channel c
-        const int32_t k = kb + kofs[i];
+        const int32_t k = kb + kofs;
         rx[sl][i] = *(const v4i*)(xsrc[i] + (int64_t)(k >> 8) * a.pH * a.pW +
                                   ((k >> 4) & 15) * a.pW);
       } else if (KTAIL) {
-        const bool ok = kb + kofs[i] < K;
-        rx[sl][i] = *(const v4i*)(xsrc[i] + (ok ? kb : 0));
+        const bool ok = kb + kofs < K;
+        rx[sl][i] = *(const v4i*)(xsrc[i] + (ok ? kb : -kofs));
         if (!ok) rx[sl][i] = zero;
       } else {
         rx[sl][i] = *(const v4i*)(xsrc[i] + kb);

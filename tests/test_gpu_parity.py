@@ -126,7 +126,11 @@ def test_linear_requant_forms(M, fallback):
 @pytest.mark.parametrize("shifts", [(15, 20), (39, 42)])
 @pytest.mark.parametrize("M,N,K", [(16448, 256, 192), (24577, 256, 192), (32640, 256, 64),
                                    (17409, 320, 192), (9408, 448, 80), (21889, 192, 256),
-                                   (27201, 192, 272), (16385, 256, 320)])
+                                   (27201, 192, 272), (16385, 256, 320),
+                                   # short and partial K steps on the tiles whose threads
+                                   # do not divide their chunks (192 channels a tile)
+                                   (66000, 192, 48), (66000, 192, 80), (33000, 384, 784),
+                                   (33000, 16, 16), (70, 48, 32)])
 def test_linear_tile_rules(M, N, K, shifts):
     """Both tiles of grids of fewer than two 128 x 128 tiles per CU (wide and
     narrow, short and longer sums, whole and partial tiles), with channels that
@@ -142,7 +146,7 @@ def test_linear_tile_rules(M, N, K, shifts):
         b[::2] = 0
     mult = g.integers(2 ** 29, 2 ** 30, N).astype(np.int32)
     shift = g.integers(*shifts, N).astype(np.int32)
-    rows = np.unique(np.r_[0:130, 0:M:53, M - 130:M])
+    rows = np.unique(np.r_[0:min(M, 130), 0:M:53, max(M - 130, 0):M])
     got = host(ilw.ilw_linear(dev(x), dev(w), dev(b), dev(mult), dev(shift)))
     assert_same(got[rows], oracle.linear(x[rows], w, b, mult, shift), "linear tile rules")
 
