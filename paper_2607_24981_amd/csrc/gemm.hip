@@ -142,16 +142,23 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
   constexpr int PW = (CW + NT - 1) / NT, PX = (CX + NT - 1) / NT;
   const int8_t* wsrc[PW];
   const int8_t* xsrc[PX];
-  const int kofs = (tid % CPR) * 16;  // the same chunk of every row a thread loads
-  static_assert(NT % CPR == 0, "kofs holds for every i");
+  int kofs[PW > PX ? PW : PX];
+  // A thread's chunk i of `chunks`, past them one of the last row that stays in
+  // the thread's column (never stored); and its offset in a row, inside it also
+  // where K is less than a step.
+  static_assert(NT % CPR == 0, "a thread loads the same column of every row");
+  auto chunk = [&](int i, int chunks) {
+    return min(tid + i * NT, chunks % NT == 0 ? chunks - 1 : chunks - CPR + tid % CPR);
+  };
+  auto col = [&](int c) { return KTAIL ? min((c % CPR) * 16, K - 16) : (c % CPR) * 16; };
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
-    const int c = min(tid + i * NT, CW - CPR + tid % CPR);
-    wsrc[i] = W + (int64_t)min(n0 + c / CPR, N - 1) * K + (c % CPR) * 16;
+    const int c = chunk(i, CW);
+    wsrc[i] = W + (int64_t)min(n0 + c / CPR, N - 1) * K + col(c);
   }
 #pragma unroll
   for (int i = 0; i < PX; ++i) {
-    const int c = min(tid + i * NT, CX - CPR + tid % CPR);
+    const int c = chunk(i, CX);
     const int64_t m = min(m0 + c / CPR, M - 1);
     if (XP) {
       // top-left pixel of the token's patch; K offsets are added per step
@@ -160,9 +167,11 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
       const uint32_t py = t / (uint32_t)a.pgw, px = t - py * (uint32_t)a.pgw;
       xsrc[i] = X + ((int64_t)b * a.pC * a.pH + (int32_t)py * 16) * a.pW + px * 16;
     } else {
-      xsrc[i] = X + m * K + (c % CPR) * 16;
+      xsrc[i] = X + m * K + col(c);
     }
   }
+#pragma unroll
+  for (int i = 0; i < (PW > PX ? PW : PX); ++i) kofs[i] = ((tid + i * NT) % CPR) * 16;
   // The loads of K step k go to register slot k % PF.
   v4i rw[PF][PW], rx[PF][PX];
   const int nk = (K + KB - 1) / KB;
@@ -171,8 +180,8 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
       if (KTAIL) {
-        const bool ok = kb + kofs < K;  // past K: the row's first chunk, never used
-        rw[sl][i] = *(const v4i*)(wsrc[i] + (ok ? kb : -kofs));
+        const bool ok = kb + kofs[i] < K;
+        rw[sl][i] = *(const v4i*)(wsrc[i] + (ok ? kb : 0));
         if (!ok) rw[sl][i] = zero;
       } else {
         rw[sl][i] = *(const v4i*)(wsrc[i] + kb);
@@ -182,12 +191,12 @@ __global__ __launch_bounds__(64 * WN * WM) void gemm_i8_kernel(GemmArgs a, uint3
     for (int i = 0; i < PX; ++i) {
       if (XP) {
         // the chunk's 16 K values are pixels kx = 0..15 of row ky of channel c
-        const int32_t k = kb + kofs;
+        const int32_t k = kb + kofs[i];
         rx[sl][i] = *(const v4i*)(xsrc[i] + (int64_t)(k >> 8) * a.pH * a.pW +
                                   ((k >> 4) & 15) * a.pW);
       } else if (KTAIL) {
-        const bool ok = kb + kofs < K;
-        rx[sl][i] = *(const v4i*)(xsrc[i] + (ok ? kb : -kofs));
+        const bool ok = kb + kofs[i] < K;
+        rx[sl][i] = *(const v4i*)(xsrc[i] + (ok ? kb : 0));
         if (!ok) rx[sl][i] = zero;
       } else {
         rx[sl][i] = *(const v4i*)(xsrc[i] + kb);

@@ -12,19 +12,21 @@ TILES = [(2, 2, 2, 2, 64), (1, 1, 4, 4, 64), (2, 2, 4, 2, 64), (3, 2, 4, 4, 64),
          (4, 2, 4, 2, 64), (6, 1, 4, 1, 64), (6, 2, 4, 2, 64), (6, 2, 4, 2, 128)]
 
 
-def chunk_ends(rows, tile_rows, threads, cpr, K, clamp_row=True):
+def chunk_ends(rows, tile_rows, threads, cpr, K, fixed=True):
     """End offsets of the 16-byte loads of the last tile of an operand of `rows`
     rows of K bytes."""
     base = (rows - 1) // tile_rows * tile_rows
     tid = np.arange(threads)[:, None, None]
     i = np.arange(-(-tile_rows * cpr // threads))[None, :, None]
     kb = np.arange(-(-K // (16 * cpr)))[None, None, :] * 16 * cpr
-    last = tile_rows * cpr - cpr + tid % cpr if clamp_row else tile_rows * cpr - 1
+    divides = tile_rows * cpr % threads == 0
+    last = tile_rows * cpr - cpr + tid % cpr if fixed and not divides else tile_rows * cpr - 1
     c = np.minimum(tid + i * threads, last)
-    src = np.minimum(base + c // cpr, rows - 1) * K + c % cpr * 16
+    col = c % cpr * 16
+    src = np.minimum(base + c // cpr, rows - 1) * K + (np.minimum(col, K - 16) if fixed else col)
     kofs = (tid + i * threads) % cpr * 16
     ok = (kb + kofs < K) if K % (16 * cpr) else np.ones_like(kb + kofs, bool)
-    return src + np.where(ok, kb, -kofs if clamp_row else 0) + 16
+    return src + np.where(ok, kb, 0) + 16
 
 
 @pytest.mark.parametrize("tile", TILES)
@@ -41,7 +43,7 @@ def test_operand_loads_stay_inside(tile):
 
 
 def test_clamped_chunk_would_run_past():
-    """Clamping the chunk, not its row, or adding a chunk's offset past K, reads
-    up to 48 bytes past the operand."""
-    assert chunk_ends(64, 64, 192, 4, 80, clamp_row=False).max() > 64 * 80
-    assert chunk_ends(64, 64, 256, 4, 16, clamp_row=False).max() == 64 * 16 + 48
+    """Clamping the chunk, not its row, or a column past K reads up to 48 bytes
+    past the operand."""
+    assert chunk_ends(64, 64, 192, 4, 80, fixed=False).max() > 64 * 80
+    assert chunk_ends(64, 64, 256, 4, 16, fixed=False).max() == 64 * 16 + 48
